@@ -52,38 +52,46 @@ constexpr unsigned kBarSpin = 1u << 24;
 enum { ST_RUNNING = 0, ST_SOLVED = 1, ST_MAX_ITER = 2, ST_NONFINITE = 3, ST_ABORTED = 4, ST_INTERNAL = 5 };
 enum { N_RP = 0, N_RD, N_AX, N_Z, N_PX, N_ATY, N_Q };
 
-__device__ __forceinline__ unsigned ld_acq(const unsigned* p) {
-  return __hip_atomic_load(p, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// Two-level grid barrier (8 groups by blockIdx % 8, then a global counter and a flag word).
-// Counters are monotone: barrier number e completes when they reach e * size. Returns false
-// if a wait exceeded the spin bound or another workgroup gave up (bar[1] set); every
-// workgroup then leaves the kernel.
+// Grid barrier: 8 arrival counters (workgroup g adds to counter g % 8), each on its own cache line
+// and monotone: barrier number e is complete when every counter has reached e * its group's size.
+// Every workgroup polls the eight counters itself (one lane each), so there is no forwarding hop:
+// a waiter reads the end of the release sequence that every arrival belongs to.
+// One wave per workgroup writes the XCD's dirty L2 lines back before the arrival (all waves of
+// the workgroup have waited for their stores first) and one invalidates after the wait; the polls
+// are relaxed. With the fences in every wave, and an acquire (an L2 invalidate) per poll, the
+// barrier cost tens of microseconds and threw the operands of running tiles out of the L2s: an
+// iteration of 128 instances took 95 us at n = m = 200 (25 now) and 345 us at n = m = 1600 (59
+// now), one of 4096 instances at n = m = 1600 took 537 us (331 now; all BF16x3).
+// Returns false if a wait exceeded the spin bound or another workgroup gave up (bar[1] set);
+// every workgroup then leaves the kernel.
 __device__ __forceinline__ bool grid_barrier(unsigned* bar, unsigned e) {
   __shared__ int ok_s;
-  // every wave's stores are made visible at device scope before its workgroup arrives
-  __threadfence();
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");  // this wave's stores have left the CU
   __syncthreads();
-  if (threadIdx.x == 0) {
-    const unsigned G = gridDim.x, g = blockIdx.x & 7u, ng = G < 8 ? G : 8;
-    const unsigned gsize = (G - g + 7u) / 8u;
+  if (threadIdx.x < 64) {
+    const unsigned G = gridDim.x, lane = threadIdx.x;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    if (lane == 0)
+      __hip_atomic_fetch_add(bar + 64 + 32 * (blockIdx.x & 7u), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const bool poll = lane < 8 && lane < G;
+    const unsigned want = e * ((G - lane + 7u) / 8u);
     int ok = 1;
-    const unsigned old = __hip_atomic_fetch_add(bar + 64 + 32 * g, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
-    if (old == e * gsize - 1u) {
-      const unsigned o2 = __hip_atomic_fetch_add(bar + 32, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
-      if (o2 == e * ng - 1u) __hip_atomic_store(bar, e, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-    }
     unsigned spins = 0;
-    while (ld_acq(bar) < e) {
-      if (++spins > kBarSpin || ld_acq(bar + 1) != 0u) {
+    while (true) {
+      const unsigned v =
+          poll ? __hip_atomic_load(bar + 64 + 32 * lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : want;
+      if (!__any((int)(poll && v < want))) break;
+      if ((++spins & 255u) == 0u &&
+          (spins > kBarSpin || __hip_atomic_load(bar + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u)) {
         ok = 0;
         __hip_atomic_store(bar + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         break;
       }
       __builtin_amdgcn_s_sleep(1);
     }
-    ok_s = ok;
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    if (lane == 0) ok_s = ok;
   }
   __syncthreads();
   return ok_s != 0;
