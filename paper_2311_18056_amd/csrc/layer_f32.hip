@@ -1,0 +1,6 @@
+// FP32 instantiations of the persistent layer kernel for plain solves.
+#include "layer_impl.h"
+
+namespace rqp {
+const void* layer_fn_f32(int nc) { return fn_for<float, false>(nc); }
+}  // namespace rqp

@@ -1,0 +1,6 @@
+// FP32 instantiations of the persistent layer kernel for closed loops and Ruiz-scaled problems.
+#include "layer_impl.h"
+
+namespace rqp {
+const void* layer_fn_f32x(int nc) { return fn_for<float, true>(nc); }
+}  // namespace rqp

@@ -1,0 +1,6 @@
+// FP64 instantiations of the persistent layer kernel for closed loops and Ruiz-scaled problems.
+#include "layer_impl.h"
+
+namespace rqp {
+const void* layer_fn_f64x(int nc) { return fn_for<double, true>(nc); }
+}  // namespace rqp

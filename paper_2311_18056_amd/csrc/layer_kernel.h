@@ -46,7 +46,9 @@ struct LayerArgs {
   const int* abort_flag;  // host-mapped int, polled at checks
   unsigned* err;        // device word: holds the tag of a solve whose exchange timed out
   int lds_rows;         // rows per block kept in LDS (set by launch_layer from the plan)
-  int check_cols;       // columns of the check vector staged in LDS at a time (set likewise)
+  int check_cols;       // entries of LDS for the check vector (set likewise)
+  int cache_bytes;      // bytes of LDS for rows of the check matrix (set likewise)
+  int col_lanes;        // lanes of a workgroup that hold columns (set likewise)
   // optional in-kernel update from initial states (x0 != null, count x nx): q = F x0,
   // l = lo - E x0, u = hi - E x0, written to q, l, u before each solve starts
   const double* x0;
@@ -85,6 +87,7 @@ constexpr int kMaxGrid = 256;
 
 // Rows per workgroup are at most kMaxRows; the host picks the grid accordingly.
 constexpr int kLayerBlock = 1024;
+constexpr int kMaxLayerRows = 8 * kLayerBlock;
 constexpr int kMaxRows = 64;
 
 // Split of the residual check over the workgroups. The check reads n L entries of [P, A'] for
@@ -119,19 +122,53 @@ inline int check_split(int g, int G, int n, int m, int L) {
 // The largest share of x rows the split gives a workgroup: at most ceil(L / G) + 1.
 constexpr int kMaxCheckRows = kMaxRows + 2;
 
-// Kernel choice and resources for a problem with L = n + m rows on `grid` workgroups: the
-// first reg_rows rows of each block stay in registers and the next lds_rows in LDS for the
-// whole solve; further rows stream from memory every iteration.
+// Rows of a block that stay in registers when a lane owns nc columns: at most 13, what
+// ceil(L / 12.5) workgroups leave a block, and at most about 64 of the 128 registers a lane of a
+// 1024-thread workgroup has.
+template <typename T>
+constexpr int layer_reg_rows(int nc) {
+  return sizeof(T) == sizeof(double) ? (nc <= 2 ? 13 : 32 / nc) : (nc <= 5 ? 13 : 64 / nc);
+}
+
+// Lanes (a multiple of the wave size) that hold the columns of the rows. A wave pays for the reduction
+// of its 13 rows over its lanes however few columns a lane has, so fewer, fuller waves run fewer
+// instructions; but every column is one more polled word per lane. In units of instructions of the
+// busiest SIMD: waves per SIMD times (13 per column plus the reduction's, about 64 in FP32 and 140 in
+// FP64), plus 90 per polled word, which puts the measured optima in order (us per iteration at 1024 /
+// 832 / 640 / 512 / 256 lanes: 3200 FP32 rows 2.97 / 2.98 / 3.09 / 3.83 / -, 2400 rows 2.71 / 2.67 / 2.77 /
+// 2.77 / -, 800 rows 1.81 / 1.80 / 1.76 / 1.72 / 1.74; 800 FP64 rows 2.44 / 2.43 / 2.29 / 2.14 / 2.83).
+template <typename T>
+inline int layer_col_lanes(int L) {
+  const int most = sizeof(T) == sizeof(double) ? 2 : 5, red = sizeof(T) == sizeof(double) ? 140 : 64;
+  int best = kLayerBlock, cost = 1 << 30;
+  for (int cs = 64; cs <= kLayerBlock; cs += 64) {
+    const int nc = (L + cs - 1) / cs;
+    if (nc > most) continue;
+    const int c = (cs + 255) / 256 * (13 * nc + red) + 90 * nc;
+    if (c < cost) {
+      best = cs;
+      cost = c;
+    }
+  }
+  return best;
+}
+
+// Kernel choice and resources for a problem on `grid` workgroups: the first layer_reg_rows rows of
+// each block stay in registers and the next lds_rows in LDS for the whole launch; further rows
+// stream from memory every iteration.
 struct LaunchPlan {
   const void* fn;
-  int reg_rows, lds_rows;
-  int check_cols;  // columns of the check vector staged in LDS at a time
+  int lds_rows;
+  int on_chip;     // rows a block can keep in registers and LDS
+  int check_cols;  // entries of LDS for the check vector
+  int cache_bytes; // LDS for rows of the check matrix
+  int col_lanes;   // lanes of a workgroup that hold columns
   size_t dyn_bytes;
-  int max_grid;  // largest cooperative grid with these resources
+  int max_grid;    // largest cooperative grid with these resources
 };
 // xt: the instantiation that also runs closed loops and Ruiz-scaled problems.
 template <typename T>
-LaunchPlan plan_layer(int L, int grid, bool xt);
+LaunchPlan plan_layer(int n, int m, int grid, bool xt);
 
 // Launch the persistent solve as a cooperative grid of `grid` workgroups of kLayerBlock threads.
 template <typename T>

@@ -421,7 +421,8 @@ int build_weights(relu_qp_handle* h, const double* P, const double* A, hipStream
 }
 
 rqp::LaunchPlan make_plan(const relu_qp_handle* h, int grid, bool xt) {
-  return h->esize == 8 ? rqp::plan_layer<double>(h->L, grid, xt) : rqp::plan_layer<float>(h->L, grid, xt);
+  return h->esize == 8 ? rqp::plan_layer<double>(h->n, h->m, grid, xt)
+                       : rqp::plan_layer<float>(h->n, h->m, grid, xt);
 }
 
 // Every workgroup's share of the check's x rows fits the kernel's buffers (kMaxCheckRows; true
@@ -471,7 +472,7 @@ int choose_grid(relu_qp_handle* h) {
   if (rc != RQP_OK) return rc;
   // plain solves: about kPlainRowsPerGroup rows per workgroup, at most the rows the kernel keeps
   // on chip (registers + LDS), and at most the grid above
-  const double on_chip = (double)(h->plan.reg_rows + h->plan.lds_rows);
+  const double on_chip = (double)h->plan.on_chip;
   int gp = (int)std::ceil(h->L / std::min(kPlainRowsPerGroup, on_chip));
   if (gp > g) gp = g;
   if (gp < need) gp = need;
@@ -866,7 +867,7 @@ int relu_qp_setup(relu_qp_handle** hp, int n, int m, const double* P, const doub
   if (rc) return rc;
   if (n < 1 || m < 1) return fail(RQP_EINVAL, "need n >= 1 and m >= 1 (n=%d, m=%d)", n, m);
   if (!P || !q || !A || !l || !u) return fail(RQP_EINVAL, "NULL problem array");
-  if ((long)n + m > 8L * rqp::kLayerBlock) return fail(RQP_EINVAL, "n + m = %ld exceeds %d", (long)n + m, 8 * rqp::kLayerBlock);
+  if ((long)n + m > rqp::kMaxLayerRows) return fail(RQP_EINVAL, "n + m = %ld exceeds %d", (long)n + m, rqp::kMaxLayerRows);
   double pmax = 0.0;
   for (long i = 0; i < (long)n * n; ++i) {
     if (!std::isfinite(P[i])) return fail(RQP_EINVAL, "P has a non-finite entry");
