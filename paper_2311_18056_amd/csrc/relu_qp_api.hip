@@ -51,8 +51,10 @@ int fail(int code, const char* fmt, ...) {
 // RAII device buffer used during setup
 struct DevBuf {
   void* p = nullptr;
-  ~DevBuf() {
+  ~DevBuf() { reset(); }
+  void reset() {
     if (p) (void)hipFree(p);
+    p = nullptr;
   }
   hipError_t alloc(size_t bytes) { return hipMalloc(&p, bytes ? bytes : 8); }
   double* d() const { return static_cast<double*>(p); }
@@ -384,40 +386,95 @@ hipError_t cast_dev(relu_qp_handle* h, long count, const double* x, void* y, hip
                        : rqp::cast_from_f64<float>(count, x, static_cast<float*>(y), st, f, period);
 }
 
+// FP64 workspace bytes of the factorisations per penalty: D_j, D_j A', A D_j A' and the inverse's panels
+// (and the assembled matrix, for the batched engine).
+size_t factor_bytes(size_t n, size_t m, bool batched) {
+  const size_t L = n + m;
+  return (n * n + m * n + m * m + (batched ? L * L : 0)) * 8 + rqp::spd_inverse_work((int)n);
+}
+// Penalties factored together: all of them while their workspace stays within 1 GiB (a family of
+// n = m = 1600 and 8 penalties takes 0.5 GiB), else as many as do, at least one. Beyond that size one
+// penalty fills the chip by itself.
+size_t factor_group(size_t n, size_t m, size_t n_rho, bool batched) {
+  const size_t fit = ((size_t)1 << 30) / factor_bytes(n, m, batched);
+  return fit < 1 ? 1 : (fit < n_rho ? fit : n_rho);
+}
+
+// Device workspace of the offline stage: P, A, A' diag(omega) A and a group of penalties' factors.
+struct SetupWork {
+  DevBuf P, A, Gw, K, DAt, ADAt, work, omega, info, Wd;
+  std::vector<double> om;  // host copy of omega, alive until the stream has been waited for
+  size_t group = 0;
+  // fewer penalties at a time where the device has no room for the full group
+  bool alloc(size_t n, size_t m, size_t n_rho, bool batched) {
+    const size_t nn = n * n, mn = m * n, mm = m * m, L = n + m;
+    if (P.alloc(nn * 8) || A.alloc(mn * 8) || Gw.alloc(nn * 8) || omega.alloc(m * 8) || info.alloc(sizeof(int)))
+      return false;
+    for (group = factor_group(n, m, n_rho, batched); group >= 1; group = group > 1 ? 1 : 0) {
+      if (!K.alloc(group * nn * 8) && !DAt.alloc(group * mn * 8) && !ADAt.alloc(group * mm * 8) &&
+          !work.alloc(group * rqp::spd_inverse_work((int)n)) && (!batched || !Wd.alloc(group * L * L * 8)))
+        return true;
+      (void)hipGetLastError();
+      for (DevBuf* b : {&K, &DAt, &ADAt, &work, &Wd}) b->reset();
+    }
+    return false;
+  }
+};
+
+// P, A, the equality weights and A' diag(omega) A on the device.
+int load_setup(relu_qp_handle* h, SetupWork& w, const double* P, const double* A, hipStream_t st) {
+  const int n = h->n, m = h->m;
+  const size_t nn = (size_t)n * n, mn = (size_t)m * n;
+  HIP_OR_FAIL(hipMemcpyAsync(w.P.p, P, nn * 8, hipMemcpyHostToDevice, st));
+  HIP_OR_FAIL(hipMemcpyAsync(w.A.p, A, mn * 8, hipMemcpyHostToDevice, st));
+  w.om.resize(m);
+  for (int i = 0; i < m; ++i) w.om[i] = h->eq[i] ? h->s.rho_eq_scale : 1.0;
+  HIP_OR_FAIL(hipMemcpyAsync(w.omega.p, w.om.data(), (size_t)m * 8, hipMemcpyHostToDevice, st));
+  HIP_OR_FAIL(hipMemsetAsync(w.info.p, 0, sizeof(int), st));
+  HIP_OR_FAIL(rqp::gemm_f64(n, n, m, 1.0, w.A.d(), 1, n, w.omega.d(), w.A.d(), n, 1, 0.0, w.Gw.d(), n, st));
+  return RQP_OK;
+}
+
+// D_j, D_j A' (n x m) and A D_j A' (m x m) of penalties j0 .. j0 + count - 1.
+int factor(relu_qp_handle* h, SetupWork& w, size_t j0, int count, hipStream_t st) {
+  const int n = h->n, m = h->m;
+  const long nn = (long)n * n, mn = (long)m * n, mm = (long)m * m;
+  HIP_OR_FAIL(rqp::kkt_form_f64(n, w.P.d(), w.Gw.d(), h->s.sigma, h->grid_d + j0, count, w.K.d(), st));
+  HIP_OR_FAIL(rqp::spd_inverse_f64(n, count, w.K.d(), w.work.d(), static_cast<int*>(w.info.p), st));
+  HIP_OR_FAIL(rqp::gemm_f64(n, m, n, 1.0, w.K.d(), n, 1, nullptr, w.A.d(), 1, n, 0.0, w.DAt.d(), m, st, count, nn, 0,
+                            mn));
+  HIP_OR_FAIL(rqp::gemm_f64(m, m, n, 1.0, w.A.d(), n, 1, nullptr, w.DAt.d(), m, 1, 0.0, w.ADAt.d(), m, st, count, 0, mn,
+                            mm));
+  return RQP_OK;
+}
+
+int finish_setup(SetupWork& w, hipStream_t st) {
+  int hinfo = 0;
+  HIP_OR_FAIL(hipMemcpyAsync(&hinfo, w.info.p, sizeof(int), hipMemcpyDeviceToHost, st));
+  HIP_OR_FAIL(hipStreamSynchronize(st));
+  if (hinfo) return fail(RQP_ENOTPD, "P + sigma I + A' diag(rho) A is not positive definite");
+  return RQP_OK;
+}
+
 // Forms the compact layer matrices [D_j, D_j A'; A D_j, A D_j A'] for every grid value and the
 // check matrix [P, A'; A, 0] (Algorithm 1, "compute KKT inverse, W and b for each rho").
 template <typename T>
 int build_weights(relu_qp_handle* h, const double* P, const double* A, hipStream_t st) {
   const int n = h->n, m = h->m;
-  DevBuf P_d, A_d, Gw, K, DAt, ADAt, work, omega, info;
-  const size_t nn = (size_t)n * n, mn = (size_t)m * n, mm = (size_t)m * m;
-  if (P_d.alloc(nn * 8) || A_d.alloc(mn * 8) || Gw.alloc(nn * 8) || K.alloc(nn * 8) || DAt.alloc(mn * 8) ||
-      ADAt.alloc(mm * 8) || work.alloc((2 * 32 * (size_t)n + 32 * 32) * 8) || omega.alloc((size_t)m * 8) ||
-      info.alloc(sizeof(int)))
-    return fail(RQP_ENOMEM, "setup workspace allocation failed (n=%d, m=%d)", n, m);
-  HIP_OR_FAIL(hipMemcpyAsync(P_d.p, P, nn * 8, hipMemcpyHostToDevice, st));
-  HIP_OR_FAIL(hipMemcpyAsync(A_d.p, A, mn * 8, hipMemcpyHostToDevice, st));
-  std::vector<double> om(m);
-  for (int i = 0; i < m; ++i) om[i] = h->eq[i] ? h->s.rho_eq_scale : 1.0;
-  HIP_OR_FAIL(hipMemcpyAsync(omega.p, om.data(), (size_t)m * 8, hipMemcpyHostToDevice, st));
-  HIP_OR_FAIL(hipMemsetAsync(info.p, 0, sizeof(int), st));
-  // Gw = A' diag(omega) A
-  HIP_OR_FAIL(rqp::gemm_f64(n, n, m, 1.0, A_d.d(), 1, n, omega.d(), A_d.d(), n, 1, 0.0, Gw.d(), n, st));
+  const size_t nr = h->grid.size();
+  SetupWork w;
+  if (!w.alloc(n, m, nr, false)) return fail(RQP_ENOMEM, "setup workspace allocation failed (n=%d, m=%d)", n, m);
+  int rc = load_setup(h, w, P, A, st);
   T* W = static_cast<T*>(h->W);
-  for (size_t j = 0; j < h->grid.size(); ++j) {
-    HIP_OR_FAIL(rqp::kkt_form_f64(n, P_d.d(), Gw.d(), h->s.sigma, h->grid[j], K.d(), st));
-    HIP_OR_FAIL(rqp::spd_inverse_f64(n, K.d(), work.d(), static_cast<int*>(info.p), st));
-    // D A'  (n x m) and A D A' (m x m)
-    HIP_OR_FAIL(rqp::gemm_f64(n, m, n, 1.0, K.d(), n, 1, nullptr, A_d.d(), 1, n, 0.0, DAt.d(), m, st));
-    HIP_OR_FAIL(rqp::gemm_f64(m, m, n, 1.0, A_d.d(), n, 1, nullptr, DAt.d(), m, 1, 0.0, ADAt.d(), m, st));
-    HIP_OR_FAIL(rqp::assemble_layer<T>(n, m, K.d(), DAt.d(), ADAt.d(), W + (long)j * h->w_stride, h->ldw, st));
+  for (size_t j = 0; j < nr && !rc; j += w.group) {
+    const int count = (int)std::min(w.group, nr - j);
+    if ((rc = factor(h, w, j, count, st))) break;
+    HIP_OR_FAIL(rqp::assemble_layer<T>(n, m, count, w.K.d(), w.DAt.d(), w.ADAt.d(), W + (long)j * h->w_stride, h->ldw,
+                                       h->w_stride, st));
   }
-  HIP_OR_FAIL(rqp::assemble_check<T>(n, m, P_d.d(), A_d.d(), static_cast<T*>(h->C), h->ldw, st));
-  int hinfo = 0;
-  HIP_OR_FAIL(hipMemcpyAsync(&hinfo, info.p, sizeof(int), hipMemcpyDeviceToHost, st));
-  HIP_OR_FAIL(hipStreamSynchronize(st));
-  if (hinfo) return fail(RQP_ENOTPD, "P + sigma I + A' diag(rho) A is not positive definite");
-  return RQP_OK;
+  if (rc) return rc;
+  HIP_OR_FAIL(rqp::assemble_check<T>(n, m, w.P.d(), w.A.d(), static_cast<T*>(h->C), h->ldw, st));
+  return finish_setup(w, st);
 }
 
 rqp::LaunchPlan make_plan(const relu_qp_handle* h, int grid, bool xt) {
@@ -525,44 +582,33 @@ int upload_f32(float* dst, const double* src, size_t count) { return upload_vec<
 int build_batch_weights(relu_qp_handle* h, const double* P, const double* A, const double* P0, const double* A0,
                         hipStream_t st) {
   const int n = h->n, m = h->m, L = h->L;
-  DevBuf P_d, A_d, Gw, K, DAt, ADAt, work, omega, info, Wd;
-  const size_t nn = (size_t)n * n, mn = (size_t)m * n, mm = (size_t)m * m, LL = (size_t)L * L;
-  if (P_d.alloc(nn * 8) || A_d.alloc(mn * 8) || Gw.alloc(nn * 8) || K.alloc(nn * 8) || DAt.alloc(mn * 8) ||
-      ADAt.alloc(mm * 8) || work.alloc((2 * 32 * (size_t)n + 32 * 32) * 8) || omega.alloc((size_t)m * 8) ||
-      info.alloc(sizeof(int)) || Wd.alloc(LL * 8))
-    return fail(RQP_ENOMEM, "setup workspace allocation failed (n=%d, m=%d)", n, m);
-  HIP_OR_FAIL(hipMemcpyAsync(P_d.p, P, nn * 8, hipMemcpyHostToDevice, st));
-  HIP_OR_FAIL(hipMemcpyAsync(A_d.p, A, mn * 8, hipMemcpyHostToDevice, st));
-  std::vector<double> om(m);
-  for (int i = 0; i < m; ++i) om[i] = h->eq[i] ? h->s.rho_eq_scale : 1.0;
-  HIP_OR_FAIL(hipMemcpyAsync(omega.p, om.data(), (size_t)m * 8, hipMemcpyHostToDevice, st));
-  HIP_OR_FAIL(hipMemsetAsync(info.p, 0, sizeof(int), st));
-  HIP_OR_FAIL(rqp::gemm_f64(n, n, m, 1.0, A_d.d(), 1, n, omega.d(), A_d.d(), n, 1, 0.0, Gw.d(), n, st));
+  const size_t nn = (size_t)n * n, mn = (size_t)m * n, LL = (size_t)L * L, nr = h->grid.size();
+  SetupWork w;
+  if (!w.alloc(n, m, nr, true)) return fail(RQP_ENOMEM, "setup workspace allocation failed (n=%d, m=%d)", n, m);
+  int rc = load_setup(h, w, P, A, st);
   const size_t es = h->bprec == rqp::kBatchBF16x3 ? 2 : 4;
-  for (size_t j = 0; j < h->grid.size(); ++j) {
-    HIP_OR_FAIL(rqp::kkt_form_f64(n, P_d.d(), Gw.d(), h->s.sigma, h->grid[j], K.d(), st));
-    HIP_OR_FAIL(rqp::spd_inverse_f64(n, K.d(), work.d(), static_cast<int*>(info.p), st));
-    HIP_OR_FAIL(rqp::gemm_f64(n, m, n, 1.0, K.d(), n, 1, nullptr, A_d.d(), 1, n, 0.0, DAt.d(), m, st));
-    HIP_OR_FAIL(rqp::gemm_f64(m, m, n, 1.0, A_d.d(), n, 1, nullptr, DAt.d(), m, 1, 0.0, ADAt.d(), m, st));
-    HIP_OR_FAIL(rqp::assemble_layer<double>(n, m, K.d(), DAt.d(), ADAt.d(), Wd.d(), L, st));
-    const size_t off = j * (size_t)h->w_stride * es;
-    if (h->bprec == rqp::kBatchBF16x3)
-      HIP_OR_FAIL(rqp::split_bf16(L, L, Wd.d(), L, static_cast<char*>(h->bWa) + off, static_cast<char*>(h->bWb) + off,
-                                  h->lpad, h->ldk, st));
-    else
-      HIP_OR_FAIL(rqp::pad_f32(L, L, Wd.d(), L, reinterpret_cast<float*>(static_cast<char*>(h->bWa) + off), h->lpad,
-                               h->ldk, st));
+  for (size_t j = 0; j < nr && !rc; j += w.group) {
+    const int count = (int)std::min(w.group, nr - j);
+    if ((rc = factor(h, w, j, count, st))) break;
+    HIP_OR_FAIL(rqp::assemble_layer<double>(n, m, count, w.K.d(), w.DAt.d(), w.ADAt.d(), w.Wd.d(), L, (long)LL, st));
+    for (int i = 0; i < count; ++i) {
+      const size_t off = (j + i) * (size_t)h->w_stride * es;
+      const double* Wi = w.Wd.d() + i * LL;
+      if (h->bprec == rqp::kBatchBF16x3)
+        HIP_OR_FAIL(rqp::split_bf16(L, L, Wi, L, static_cast<char*>(h->bWa) + off, static_cast<char*>(h->bWb) + off,
+                                    h->lpad, h->ldk, st));
+      else
+        HIP_OR_FAIL(rqp::pad_f32(L, L, Wi, L, reinterpret_cast<float*>(static_cast<char*>(h->bWa) + off), h->lpad,
+                                 h->ldk, st));
+    }
   }
+  if (rc) return rc;
   // the check matrix stays FP64 (the residuals are FP64 evaluations of the iterates)
-  if (P0 != P) HIP_OR_FAIL(hipMemcpyAsync(P_d.p, P0, nn * 8, hipMemcpyHostToDevice, st));
-  if (A0 != A) HIP_OR_FAIL(hipMemcpyAsync(A_d.p, A0, mn * 8, hipMemcpyHostToDevice, st));
-  HIP_OR_FAIL(rqp::assemble_check<double>(n, m, P_d.d(), A_d.d(), Wd.d(), L, st));
-  HIP_OR_FAIL(rqp::pad_f64(L, L, Wd.d(), L, h->bCd, h->cpad, h->ldk, st));
-  int hinfo = 0;
-  HIP_OR_FAIL(hipMemcpyAsync(&hinfo, info.p, sizeof(int), hipMemcpyDeviceToHost, st));
-  HIP_OR_FAIL(hipStreamSynchronize(st));
-  if (hinfo) return fail(RQP_ENOTPD, "P + sigma I + A' diag(rho) A is not positive definite");
-  return RQP_OK;
+  if (P0 != P) HIP_OR_FAIL(hipMemcpyAsync(w.P.p, P0, nn * 8, hipMemcpyHostToDevice, st));
+  if (A0 != A) HIP_OR_FAIL(hipMemcpyAsync(w.A.p, A0, mn * 8, hipMemcpyHostToDevice, st));
+  HIP_OR_FAIL(rqp::assemble_check<double>(n, m, w.P.d(), w.A.d(), w.Wd.d(), L, st));
+  HIP_OR_FAIL(rqp::pad_f64(L, L, w.Wd.d(), L, h->bCd, h->cpad, h->ldk, st));
+  return finish_setup(w, st);
 }
 
 int autotune_tiles(relu_qp_handle* h, hipStream_t st);
@@ -1736,10 +1782,9 @@ int relu_qp_footprint(int n, int m, const relu_qp_settings* s, int nx, size_t* b
   if (nx > 0) t += ((size_t)n + m) * nx * 8 + 2 * (size_t)m * 8;
   *bytes = t;
   if (setup_extra) {
-    const size_t nn = (size_t)n * n, mn = (size_t)m * n, mm = (size_t)m * m;
-    size_t w = (3 * nn + 2 * mn + mm + 2 * 32 * (size_t)n + 32 * 32 + m) * 8 + sizeof(int);
-    if (is_batched(*s)) w += L * L * 8;
-    *setup_extra = w;
+    const size_t nn = (size_t)n * n, mn = (size_t)m * n;
+    const bool batched = is_batched(*s);
+    *setup_extra = (2 * nn + mn + m) * 8 + sizeof(int) + factor_group(n, m, nr, batched) * factor_bytes(n, m, batched);
   }
   return RQP_OK;
 }

@@ -19,7 +19,11 @@ constexpr int SB = 32;  // Gauss-Jordan pivot block
 __global__ void __launch_bounds__(256) gemm_f64_kernel(int M, int N, int K, double alpha, const double* __restrict__ A,
                                                        long a_rs, long a_cs, const double* __restrict__ ks,
                                                        const double* __restrict__ B, long b_rs, long b_cs, double beta,
-                                                       double* __restrict__ C, long ldc) {
+                                                       double* __restrict__ C, long ldc, long a_bs, long b_bs,
+                                                       long c_bs) {
+  A += blockIdx.z * a_bs;
+  B += blockIdx.z * b_bs;
+  C += blockIdx.z * c_bs;
   __shared__ double As[GK][GT + 1];
   __shared__ double Bs[GK][GT + 1];
   const int tid = threadIdx.x;
@@ -92,19 +96,27 @@ __global__ void __launch_bounds__(256) gemm_f64_kernel(int M, int N, int K, doub
 }
 
 __global__ void kkt_form_kernel(int n, const double* __restrict__ P, const double* __restrict__ Gw, double sigma,
-                                double rho, double* __restrict__ K) {
+                                const double* __restrict__ rho, double* __restrict__ K) {
   long idx = (long)blockIdx.x * blockDim.x + threadIdx.x;
   long total = (long)n * n;
   if (idx >= total) return;
   int i = (int)(idx / n), j = (int)(idx % n);
-  double v = P[idx] + rho * Gw[idx];
+  double v = P[idx] + rho[blockIdx.z] * Gw[idx];
   if (i == j) v += sigma;
-  K[idx] = v;
+  K[blockIdx.z * total + idx] = v;
 }
+
+// The Gauss-Jordan kernels take one matrix per blockIdx.z (the penalties' matrices are independent):
+// a step of one 600 x 600 matrix is three launches of latency (20, 12 and 20 us measured) that leave
+// the chip idle, so the matrices of all penalties go through each step together. Same arithmetic and
+// order per matrix. work: gj_work(n) doubles per matrix (pivot inverse, row panel, old column panel).
+__host__ __device__ inline long gj_work(int n) { return SB * SB + 2L * SB * n; }
 
 // Inverse of the pivot block (bb x bb, bb <= 32) by unblocked Gauss-Jordan in LDS.
 __global__ void __launch_bounds__(1024) gj_diag_kernel(const double* __restrict__ M, int n, int pb, int bb,
                                                        double* __restrict__ Pinv, int* __restrict__ info) {
+  M += blockIdx.z * (long)n * n;
+  Pinv += blockIdx.z * gj_work(n);
   __shared__ double S[SB][SB + 1];
   const int r = threadIdx.x / SB, c = threadIdx.x % SB;
   const bool act = r < bb && c < bb;
@@ -138,6 +150,10 @@ __global__ void __launch_bounds__(1024) gj_diag_kernel(const double* __restrict_
 __global__ void __launch_bounds__(256) gj_panel_kernel(const double* __restrict__ M, int n, int pb, int bb,
                                                        const double* __restrict__ Pinv, double* __restrict__ R,
                                                        double* __restrict__ Cold) {
+  M += blockIdx.z * (long)n * n;
+  Pinv += blockIdx.z * gj_work(n);
+  R += blockIdx.z * gj_work(n);
+  Cold += blockIdx.z * gj_work(n);
   __shared__ double Ps[SB][SB + 1];
   __shared__ double Ms[SB][GT + 1];
   const int tid = threadIdx.x;
@@ -169,6 +185,10 @@ __global__ void __launch_bounds__(256) gj_panel_kernel(const double* __restrict_
 __global__ void __launch_bounds__(256) gj_update_kernel(double* __restrict__ M, int n, int pb, int bb,
                                                         const double* __restrict__ Pinv, const double* __restrict__ R,
                                                         const double* __restrict__ Cold) {
+  M += blockIdx.z * (long)n * n;
+  Pinv += blockIdx.z * gj_work(n);
+  R += blockIdx.z * gj_work(n);
+  Cold += blockIdx.z * gj_work(n);
   __shared__ double Cs[SB][GT + 1];  // Cs[t][i] = Cold[i0 + i][t]
   __shared__ double Rs[SB][GT + 1];  // Rs[t][j] = R[t][j0 + j]
   __shared__ double Ps[SB][SB + 1];
@@ -220,6 +240,7 @@ __global__ void __launch_bounds__(256) gj_update_kernel(double* __restrict__ M, 
 __global__ void symmetrize_kernel(int n, double* __restrict__ M) {
   long idx = (long)blockIdx.x * blockDim.x + threadIdx.x;
   if (idx >= (long)n * n) return;
+  M += blockIdx.z * (long)n * n;
   int i = (int)(idx / n), j = (int)(idx % n);
   if (i >= j) return;
   double a = M[(long)i * n + j], b = M[(long)j * n + i];
@@ -230,8 +251,12 @@ __global__ void symmetrize_kernel(int n, double* __restrict__ M) {
 
 template <typename T>
 __global__ void assemble_layer_kernel(int n, int m, const double* __restrict__ D, const double* __restrict__ DAt,
-                                      const double* __restrict__ ADAt, T* __restrict__ W, long ldw) {
+                                      const double* __restrict__ ADAt, T* __restrict__ W, long ldw, long w_bs) {
   const int L = n + m;
+  D += blockIdx.z * (long)n * n;
+  DAt += blockIdx.z * (long)n * m;
+  ADAt += blockIdx.z * (long)m * m;
+  W += blockIdx.z * w_bs;
   long idx = (long)blockIdx.x * blockDim.x + threadIdx.x;
   if (idx >= (long)L * ldw) return;
   int i = (int)(idx / ldw), j = (int)(idx % ldw);
@@ -355,44 +380,49 @@ inline unsigned blocks_for(long count, int bs) { return (unsigned)((count + bs -
 }  // namespace
 
 hipError_t gemm_f64(int M, int N, int K, double alpha, const double* A, long a_rs, long a_cs, const double* kscale,
-                    const double* B, long b_rs, long b_cs, double beta, double* C, long ldc, hipStream_t st) {
-  if (M <= 0 || N <= 0) return hipSuccess;
-  dim3 grid((N + GT - 1) / GT, (M + GT - 1) / GT);
+                    const double* B, long b_rs, long b_cs, double beta, double* C, long ldc, hipStream_t st, int count,
+                    long a_bs, long b_bs, long c_bs) {
+  if (M <= 0 || N <= 0 || count <= 0) return hipSuccess;
+  dim3 grid((N + GT - 1) / GT, (M + GT - 1) / GT, count);
   hipLaunchKernelGGL(gemm_f64_kernel, grid, dim3(256), 0, st, M, N, K, alpha, A, a_rs, a_cs, kscale, B, b_rs, b_cs,
-                     beta, C, ldc);
+                     beta, C, ldc, a_bs, b_bs, c_bs);
   return hipGetLastError();
 }
 
-hipError_t kkt_form_f64(int n, const double* P, const double* Gw, double sigma, double rho, double* K, hipStream_t st) {
+hipError_t kkt_form_f64(int n, const double* P, const double* Gw, double sigma, const double* rho, int count, double* K,
+                        hipStream_t st) {
   long total = (long)n * n;
-  hipLaunchKernelGGL(kkt_form_kernel, dim3(blocks_for(total, 256)), dim3(256), 0, st, n, P, Gw, sigma, rho, K);
+  hipLaunchKernelGGL(kkt_form_kernel, dim3(blocks_for(total, 256), 1, count), dim3(256), 0, st, n, P, Gw, sigma, rho,
+                     K);
   return hipGetLastError();
 }
 
-hipError_t spd_inverse_f64(int n, double* M, double* work, int* info, hipStream_t st) {
+size_t spd_inverse_work(int n) { return (size_t)gj_work(n) * 8; }
+
+hipError_t spd_inverse_f64(int n, int count, double* M, double* work, int* info, hipStream_t st) {
   double* Pinv = work;
   double* R = work + SB * SB;
   double* Cold = R + (long)SB * n;
-  const unsigned ct = (n + GT - 1) / GT;
+  const unsigned ct = (n + GT - 1) / GT, z = count;
   for (int pb = 0; pb < n; pb += SB) {
     int bb = n - pb < SB ? n - pb : SB;
-    hipLaunchKernelGGL(gj_diag_kernel, dim3(1), dim3(SB * SB), 0, st, M, n, pb, bb, Pinv, info);
-    hipLaunchKernelGGL(gj_panel_kernel, dim3(ct), dim3(256), 0, st, M, n, pb, bb, Pinv, R, Cold);
-    hipLaunchKernelGGL(gj_update_kernel, dim3(ct, ct), dim3(256), 0, st, M, n, pb, bb, Pinv, R, Cold);
+    hipLaunchKernelGGL(gj_diag_kernel, dim3(1, 1, z), dim3(SB * SB), 0, st, M, n, pb, bb, Pinv, info);
+    hipLaunchKernelGGL(gj_panel_kernel, dim3(ct, 1, z), dim3(256), 0, st, M, n, pb, bb, Pinv, R, Cold);
+    hipLaunchKernelGGL(gj_update_kernel, dim3(ct, ct, z), dim3(256), 0, st, M, n, pb, bb, Pinv, R, Cold);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
   long total = (long)n * n;
-  hipLaunchKernelGGL(symmetrize_kernel, dim3(blocks_for(total, 256)), dim3(256), 0, st, n, M);
+  hipLaunchKernelGGL(symmetrize_kernel, dim3(blocks_for(total, 256), 1, z), dim3(256), 0, st, n, M);
   return hipGetLastError();
 }
 
 template <typename T>
-hipError_t assemble_layer(int n, int m, const double* D, const double* DAt, const double* ADAt, T* W, long ldw,
-                          hipStream_t st) {
+hipError_t assemble_layer(int n, int m, int count, const double* D, const double* DAt, const double* ADAt, T* W,
+                          long ldw, long w_bs, hipStream_t st) {
   long total = (long)(n + m) * ldw;
-  hipLaunchKernelGGL(assemble_layer_kernel<T>, dim3(blocks_for(total, 256)), dim3(256), 0, st, n, m, D, DAt, ADAt, W,
-                     ldw);
+  hipLaunchKernelGGL(assemble_layer_kernel<T>, dim3(blocks_for(total, 256), 1, count), dim3(256), 0, st, n, m, D, DAt,
+                     ADAt, W, ldw, w_bs);
   return hipGetLastError();
 }
 
@@ -428,10 +458,10 @@ hipError_t cast_from_f64(long count, const double* x, T* y, hipStream_t st, cons
   return hipGetLastError();
 }
 
-template hipError_t assemble_layer<float>(int, int, const double*, const double*, const double*, float*, long,
+template hipError_t assemble_layer<float>(int, int, int, const double*, const double*, const double*, float*, long, long,
                                           hipStream_t);
-template hipError_t assemble_layer<double>(int, int, const double*, const double*, const double*, double*, long,
-                                           hipStream_t);
+template hipError_t assemble_layer<double>(int, int, int, const double*, const double*, const double*, double*, long, long,
+                                          hipStream_t);
 template hipError_t assemble_check<float>(int, int, const double*, const double*, float*, long, hipStream_t);
 template hipError_t assemble_check<double>(int, int, const double*, const double*, double*, long, hipStream_t);
 template hipError_t mpc_vectors<float>(int, int, int, int, const double*, const double*, const double*,
