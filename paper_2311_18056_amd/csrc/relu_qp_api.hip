@@ -400,24 +400,44 @@ size_t factor_group(size_t n, size_t m, size_t n_rho, bool batched) {
   return fit < 1 ? 1 : (fit < n_rho ? fit : n_rho);
 }
 
-// Device workspace of the offline stage: P, A, A' diag(omega) A and a group of penalties' factors.
+// Device workspace of the offline stage: P, A, A' diag(omega) A and a group of penalties' factors, in one
+// allocation (a free costs about 44 us of host time).
 struct SetupWork {
-  DevBuf P, A, Gw, K, DAt, ADAt, work, omega, info, Wd;
+  DevBuf mem;
+  double *P = nullptr, *A = nullptr, *Gw = nullptr, *K = nullptr, *DAt = nullptr, *ADAt = nullptr, *work = nullptr,
+         *omega = nullptr, *Wd = nullptr;
+  int* info = nullptr;
   std::vector<double> om;  // host copy of omega, alive until the stream has been waited for
   size_t group = 0;
+  static size_t bytes(size_t n, size_t m, size_t group, bool batched) {
+    return (2 * n * n + m * n + m) * 8 + sizeof(int) + group * factor_bytes(n, m, batched) + 16 * 256;
+  }
   // fewer penalties at a time where the device has no room for the full group
   bool alloc(size_t n, size_t m, size_t n_rho, bool batched) {
     const size_t nn = n * n, mn = m * n, mm = m * m, L = n + m;
-    if (P.alloc(nn * 8) || A.alloc(mn * 8) || Gw.alloc(nn * 8) || omega.alloc(m * 8) || info.alloc(sizeof(int)))
-      return false;
-    for (group = factor_group(n, m, n_rho, batched); group >= 1; group = group > 1 ? 1 : 0) {
-      if (!K.alloc(group * nn * 8) && !DAt.alloc(group * mn * 8) && !ADAt.alloc(group * mm * 8) &&
-          !work.alloc(group * rqp::spd_inverse_work((int)n)) && (!batched || !Wd.alloc(group * L * L * 8)))
-        return true;
+    group = factor_group(n, m, n_rho, batched);
+    if (mem.alloc(bytes(n, m, group, batched)) != hipSuccess) {
       (void)hipGetLastError();
-      for (DevBuf* b : {&K, &DAt, &ADAt, &work, &Wd}) b->reset();
+      group = 1;
+      if (mem.alloc(bytes(n, m, 1, batched)) != hipSuccess) return false;
     }
-    return false;
+    char* p = static_cast<char*>(mem.p);
+    auto take = [&p](size_t b) {
+      double* const q = reinterpret_cast<double*>(p);
+      p += (b + 255) / 256 * 256;
+      return q;
+    };
+    P = take(nn * 8);
+    A = take(mn * 8);
+    Gw = take(nn * 8);
+    omega = take(m * 8);
+    info = reinterpret_cast<int*>(take(sizeof(int)));
+    K = take(group * nn * 8);
+    DAt = take(group * mn * 8);
+    ADAt = take(group * mm * 8);
+    work = take(group * rqp::spd_inverse_work((int)n));
+    if (batched) Wd = take(group * L * L * 8);
+    return true;
   }
 };
 
@@ -425,13 +445,13 @@ struct SetupWork {
 int load_setup(relu_qp_handle* h, SetupWork& w, const double* P, const double* A, hipStream_t st) {
   const int n = h->n, m = h->m;
   const size_t nn = (size_t)n * n, mn = (size_t)m * n;
-  HIP_OR_FAIL(hipMemcpyAsync(w.P.p, P, nn * 8, hipMemcpyHostToDevice, st));
-  HIP_OR_FAIL(hipMemcpyAsync(w.A.p, A, mn * 8, hipMemcpyHostToDevice, st));
+  HIP_OR_FAIL(hipMemcpyAsync(w.P, P, nn * 8, hipMemcpyHostToDevice, st));
+  HIP_OR_FAIL(hipMemcpyAsync(w.A, A, mn * 8, hipMemcpyHostToDevice, st));
   w.om.resize(m);
   for (int i = 0; i < m; ++i) w.om[i] = h->eq[i] ? h->s.rho_eq_scale : 1.0;
-  HIP_OR_FAIL(hipMemcpyAsync(w.omega.p, w.om.data(), (size_t)m * 8, hipMemcpyHostToDevice, st));
-  HIP_OR_FAIL(hipMemsetAsync(w.info.p, 0, sizeof(int), st));
-  HIP_OR_FAIL(rqp::gemm_f64(n, n, m, 1.0, w.A.d(), 1, n, w.omega.d(), w.A.d(), n, 1, 0.0, w.Gw.d(), n, st));
+  HIP_OR_FAIL(hipMemcpyAsync(w.omega, w.om.data(), (size_t)m * 8, hipMemcpyHostToDevice, st));
+  HIP_OR_FAIL(hipMemsetAsync(w.info, 0, sizeof(int), st));
+  HIP_OR_FAIL(rqp::gemm_f64(n, n, m, 1.0, w.A, 1, n, w.omega, w.A, n, 1, 0.0, w.Gw, n, st));
   return RQP_OK;
 }
 
@@ -439,18 +459,18 @@ int load_setup(relu_qp_handle* h, SetupWork& w, const double* P, const double* A
 int factor(relu_qp_handle* h, SetupWork& w, size_t j0, int count, hipStream_t st) {
   const int n = h->n, m = h->m;
   const long nn = (long)n * n, mn = (long)m * n, mm = (long)m * m;
-  HIP_OR_FAIL(rqp::kkt_form_f64(n, w.P.d(), w.Gw.d(), h->s.sigma, h->grid_d + j0, count, w.K.d(), st));
-  HIP_OR_FAIL(rqp::spd_inverse_f64(n, count, w.K.d(), w.work.d(), static_cast<int*>(w.info.p), st));
-  HIP_OR_FAIL(rqp::gemm_f64(n, m, n, 1.0, w.K.d(), n, 1, nullptr, w.A.d(), 1, n, 0.0, w.DAt.d(), m, st, count, nn, 0,
+  HIP_OR_FAIL(rqp::kkt_form_f64(n, w.P, w.Gw, h->s.sigma, h->grid_d + j0, count, w.K, st));
+  HIP_OR_FAIL(rqp::spd_inverse_f64(n, count, w.K, w.work, w.info, st));
+  HIP_OR_FAIL(rqp::gemm_f64(n, m, n, 1.0, w.K, n, 1, nullptr, w.A, 1, n, 0.0, w.DAt, m, st, count, nn, 0,
                             mn));
-  HIP_OR_FAIL(rqp::gemm_f64(m, m, n, 1.0, w.A.d(), n, 1, nullptr, w.DAt.d(), m, 1, 0.0, w.ADAt.d(), m, st, count, 0, mn,
+  HIP_OR_FAIL(rqp::gemm_f64(m, m, n, 1.0, w.A, n, 1, nullptr, w.DAt, m, 1, 0.0, w.ADAt, m, st, count, 0, mn,
                             mm));
   return RQP_OK;
 }
 
 int finish_setup(SetupWork& w, hipStream_t st) {
   int hinfo = 0;
-  HIP_OR_FAIL(hipMemcpyAsync(&hinfo, w.info.p, sizeof(int), hipMemcpyDeviceToHost, st));
+  HIP_OR_FAIL(hipMemcpyAsync(&hinfo, w.info, sizeof(int), hipMemcpyDeviceToHost, st));
   HIP_OR_FAIL(hipStreamSynchronize(st));
   if (hinfo) return fail(RQP_ENOTPD, "P + sigma I + A' diag(rho) A is not positive definite");
   return RQP_OK;
@@ -469,11 +489,11 @@ int build_weights(relu_qp_handle* h, const double* P, const double* A, hipStream
   for (size_t j = 0; j < nr && !rc; j += w.group) {
     const int count = (int)std::min(w.group, nr - j);
     if ((rc = factor(h, w, j, count, st))) break;
-    HIP_OR_FAIL(rqp::assemble_layer<T>(n, m, count, w.K.d(), w.DAt.d(), w.ADAt.d(), W + (long)j * h->w_stride, h->ldw,
+    HIP_OR_FAIL(rqp::assemble_layer<T>(n, m, count, w.K, w.DAt, w.ADAt, W + (long)j * h->w_stride, h->ldw,
                                        h->w_stride, st));
   }
   if (rc) return rc;
-  HIP_OR_FAIL(rqp::assemble_check<T>(n, m, w.P.d(), w.A.d(), static_cast<T*>(h->C), h->ldw, st));
+  HIP_OR_FAIL(rqp::assemble_check<T>(n, m, w.P, w.A, static_cast<T*>(h->C), h->ldw, st));
   return finish_setup(w, st);
 }
 
@@ -590,10 +610,10 @@ int build_batch_weights(relu_qp_handle* h, const double* P, const double* A, con
   for (size_t j = 0; j < nr && !rc; j += w.group) {
     const int count = (int)std::min(w.group, nr - j);
     if ((rc = factor(h, w, j, count, st))) break;
-    HIP_OR_FAIL(rqp::assemble_layer<double>(n, m, count, w.K.d(), w.DAt.d(), w.ADAt.d(), w.Wd.d(), L, (long)LL, st));
+    HIP_OR_FAIL(rqp::assemble_layer<double>(n, m, count, w.K, w.DAt, w.ADAt, w.Wd, L, (long)LL, st));
     for (int i = 0; i < count; ++i) {
       const size_t off = (j + i) * (size_t)h->w_stride * es;
-      const double* Wi = w.Wd.d() + i * LL;
+      const double* Wi = w.Wd + i * LL;
       if (h->bprec == rqp::kBatchBF16x3)
         HIP_OR_FAIL(rqp::split_bf16(L, L, Wi, L, static_cast<char*>(h->bWa) + off, static_cast<char*>(h->bWb) + off,
                                     h->lpad, h->ldk, st));
@@ -604,10 +624,10 @@ int build_batch_weights(relu_qp_handle* h, const double* P, const double* A, con
   }
   if (rc) return rc;
   // the check matrix stays FP64 (the residuals are FP64 evaluations of the iterates)
-  if (P0 != P) HIP_OR_FAIL(hipMemcpyAsync(w.P.p, P0, nn * 8, hipMemcpyHostToDevice, st));
-  if (A0 != A) HIP_OR_FAIL(hipMemcpyAsync(w.A.p, A0, mn * 8, hipMemcpyHostToDevice, st));
-  HIP_OR_FAIL(rqp::assemble_check<double>(n, m, w.P.d(), w.A.d(), w.Wd.d(), L, st));
-  HIP_OR_FAIL(rqp::pad_f64(L, L, w.Wd.d(), L, h->bCd, h->cpad, h->ldk, st));
+  if (P0 != P) HIP_OR_FAIL(hipMemcpyAsync(w.P, P0, nn * 8, hipMemcpyHostToDevice, st));
+  if (A0 != A) HIP_OR_FAIL(hipMemcpyAsync(w.A, A0, mn * 8, hipMemcpyHostToDevice, st));
+  HIP_OR_FAIL(rqp::assemble_check<double>(n, m, w.P, w.A, w.Wd, L, st));
+  HIP_OR_FAIL(rqp::pad_f64(L, L, w.Wd, L, h->bCd, h->cpad, h->ldk, st));
   return finish_setup(w, st);
 }
 
@@ -1782,9 +1802,8 @@ int relu_qp_footprint(int n, int m, const relu_qp_settings* s, int nx, size_t* b
   if (nx > 0) t += ((size_t)n + m) * nx * 8 + 2 * (size_t)m * 8;
   *bytes = t;
   if (setup_extra) {
-    const size_t nn = (size_t)n * n, mn = (size_t)m * n;
     const bool batched = is_batched(*s);
-    *setup_extra = (2 * nn + mn + m) * 8 + sizeof(int) + factor_group(n, m, nr, batched) * factor_bytes(n, m, batched);
+    *setup_extra = SetupWork::bytes(n, m, factor_group(n, m, nr, batched), batched);
   }
   return RQP_OK;
 }

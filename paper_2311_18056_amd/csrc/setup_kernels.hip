@@ -12,10 +12,52 @@ namespace rqp {
 
 namespace {
 
-constexpr int GT = 64;  // GEMM output tile edge
+constexpr int GT = 64;  // edge of the small output tiles
 constexpr int GK = 16;  // GEMM k-step
 constexpr int SB = 32;  // Gauss-Jordan pivot block
 
+typedef double doublex4 __attribute__((ext_vector_type(4)));
+// LDS row pitch of a panel: a fragment read (16 columns of rows k and k + 1 per half wave)
+// and a store of 16 rows by 2 columns both fall on (nearly) distinct banks.
+constexpr int GP = GT + 18;
+
+// acc[a][b] += A^T B over kk in [0, KK) of the LDS panels As[kk][row], Bs[kk][col], for this wave's
+// quarter of a 64 x 64 tile: blocks of v_mfma_f64_16x16x4f64. The instruction adds its four products one
+// after another in k order, each with its own rounding (checked on the device, bit for bit, against a
+// chain of FMAs), so an element is one FMA chain over ascending k whatever the tiling.
+template <int KK>
+__device__ __forceinline__ void mfma_tile(const double (*As)[GP], const double (*Bs)[GP], doublex4 (&acc)[2][2]) {
+  const int lane = threadIdx.x % 64, wave = threadIdx.x / 64;
+  const int r = (wave / 2) * 32 + lane % 16, c = (wave % 2) * 32 + lane % 16;
+#pragma unroll
+  for (int k4 = 0; k4 < KK; k4 += 4) {
+    const int kk = k4 + lane / 16;
+    double av[2], bv[2];
+#pragma unroll
+    for (int a = 0; a < 2; ++a) av[a] = As[kk][r + 16 * a];
+#pragma unroll
+    for (int b = 0; b < 2; ++b) bv[b] = Bs[kk][c + 16 * b];
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int b = 0; b < 2; ++b)
+        acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[a], bv[b], acc[a][b], 0, 0, 0);
+  }
+}
+// Tile position of element v of block (a, b) for this lane.
+__device__ __forceinline__ int tile_row(int a, int v) {
+  return (threadIdx.x / 128) * 32 + 16 * a + (threadIdx.x % 64) / 16 + 4 * v;
+}
+__device__ __forceinline__ int tile_col(int b) {
+  return (threadIdx.x / 64 % 2) * 32 + 16 * b + threadIdx.x % 16;
+}
+
+// One 64 x 64 tile of C per workgroup, four waves; the next K stage's elements are loaded into registers
+// while a stage is multiplied. Bound by the FP64 matrix cores and by what hides the loads: 8 products of
+// 1800 x 1800 x 600 take 791 us (39 TFLOP/s of 67 that a large library product reaches here), with
+// 128 x 128 tiles (two workgroups per compute unit instead of four) 1025 us. The three products of a set-up
+// of n = 600, m = 1800 with 8 penalties take 1.31 ms; on the vector units, with a bounds test per element,
+// they took 2.22 ms.
 __global__ void __launch_bounds__(256) gemm_f64_kernel(int M, int N, int K, double alpha, const double* __restrict__ A,
                                                        long a_rs, long a_cs, const double* __restrict__ ks,
                                                        const double* __restrict__ B, long b_rs, long b_cs, double beta,
@@ -24,75 +66,75 @@ __global__ void __launch_bounds__(256) gemm_f64_kernel(int M, int N, int K, doub
   A += blockIdx.z * a_bs;
   B += blockIdx.z * b_bs;
   C += blockIdx.z * c_bs;
-  __shared__ double As[GK][GT + 1];
-  __shared__ double Bs[GK][GT + 1];
+  __shared__ double As[GK][GP];
+  __shared__ double Bs[GK][GP];
   const int tid = threadIdx.x;
-  const int tx = tid % 16, ty = tid / 16;
   const int i0 = blockIdx.y * GT, j0 = blockIdx.x * GT;
   const bool a_kfast = a_cs == 1;  // consecutive k contiguous in memory
   const bool b_jfast = b_cs == 1;
-  double acc[4][4];
+  // element i of this thread: of A's panel row ar + i adr, k step ak + i adk; of B's likewise
+  constexpr int E = GT * GK / 256;
+  const int ar = a_kfast ? tid / GK : tid % GT, adr = a_kfast ? 256 / GK : 0;
+  const int ak = a_kfast ? tid % GK : tid / GT, adk = a_kfast ? 0 : 256 / GT;
+  const int bc = b_jfast ? tid % GT : tid / GK, bdc = b_jfast ? 0 : 256 / GK;
+  const int bk = b_jfast ? tid / GT : tid % GK, bdk = b_jfast ? 256 / GT : 0;
+  const double* const pa = A + (long)(i0 + ar) * a_rs + (long)ak * a_cs;
+  const double* const pb = B + (long)bk * b_rs + (long)(j0 + bc) * b_cs;
+  const long sa = adr * a_rs + adk * a_cs, sb = bdc * b_cs + bdk * b_rs;
+  const bool inside = i0 + GT <= M && j0 + GT <= N;
+  double ra[E], rb[E], rs[E];
+  auto load = [&](int k0) {
+    const double* const qa = pa + k0 * a_cs;
+    const double* const qb = pb + k0 * b_rs;
+    if (inside && k0 + GK <= K) {  // no per-element tests: all loads of the stage in flight together
 #pragma unroll
-  for (int a = 0; a < 4; ++a)
+      for (int i = 0; i < E; ++i) {
+        ra[i] = qa[i * sa];
+        rb[i] = qb[i * sb];
+      }
+    } else {
 #pragma unroll
-    for (int b = 0; b < 4; ++b) acc[a][b] = 0.0;
-
+      for (int i = 0; i < E; ++i) {
+        ra[i] = i0 + ar + i * adr < M && k0 + ak + i * adk < K ? qa[i * sa] : 0.0;
+        rb[i] = j0 + bc + i * bdc < N && k0 + bk + i * bdk < K ? qb[i * sb] : 0.0;
+      }
+    }
+    if (ks) {
+#pragma unroll
+      for (int i = 0; i < E; ++i) rs[i] = k0 + ak + i * adk < K ? ks[k0 + ak + i * adk] : 0.0;
+    }
+  };
+  doublex4 acc[2][2];
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int b = 0; b < 2; ++b) acc[a][b] = doublex4{0.0, 0.0, 0.0, 0.0};
+  load(0);
   for (int k0 = 0; k0 < K; k0 += GK) {
-    for (int e = tid; e < GT * GK; e += 256) {
-      int r, kk;
-      if (a_kfast) {
-        r = e / GK;
-        kk = e % GK;
-      } else {
-        kk = e / GT;
-        r = e % GT;
-      }
-      int gi = i0 + r, gk = k0 + kk;
-      double v = 0.0;
-      if (gi < M && gk < K) {
-        v = A[(long)gi * a_rs + (long)gk * a_cs];
-        if (ks) v *= ks[gk];
-      }
-      As[kk][r] = v;
-      int c;
-      if (b_jfast) {
-        kk = e / GT;
-        c = e % GT;
-      } else {
-        c = e / GK;
-        kk = e % GK;
-      }
-      int gj = j0 + c;
-      gk = k0 + kk;
-      Bs[kk][c] = (gj < N && gk < K) ? B[(long)gk * b_rs + (long)gj * b_cs] : 0.0;
-    }
     __syncthreads();
 #pragma unroll
-    for (int kk = 0; kk < GK; ++kk) {
-      double av[4], bv[4];
-#pragma unroll
-      for (int a = 0; a < 4; ++a) av[a] = As[kk][ty + 16 * a];
-#pragma unroll
-      for (int b = 0; b < 4; ++b) bv[b] = Bs[kk][tx + 16 * b];
-#pragma unroll
-      for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int b = 0; b < 4; ++b) acc[a][b] = fma(av[a], bv[b], acc[a][b]);
+    for (int i = 0; i < E; ++i) {
+      As[ak + i * adk][ar + i * adr] = ks ? ra[i] * rs[i] : ra[i];
+      Bs[bk + i * bdk][bc + i * bdc] = rb[i];
     }
     __syncthreads();
+    if (k0 + GK < K) load(k0 + GK);
+    mfma_tile<GK>(As, Bs, acc);
   }
 #pragma unroll
-  for (int a = 0; a < 4; ++a) {
-    int gi = i0 + ty + 16 * a;
-    if (gi >= M) continue;
+  for (int a = 0; a < 2; ++a)
 #pragma unroll
-    for (int b = 0; b < 4; ++b) {
-      int gj = j0 + tx + 16 * b;
-      if (gj >= N) continue;
-      double* c = C + (long)gi * ldc + gj;
-      *c = (beta == 0.0) ? alpha * acc[a][b] : alpha * acc[a][b] + beta * (*c);
+    for (int v = 0; v < 4; ++v) {
+      const int gi = i0 + tile_row(a, v);
+      if (gi >= M) continue;
+#pragma unroll
+      for (int b = 0; b < 2; ++b) {
+        const int gj = j0 + tile_col(b);
+        if (gj >= N) continue;
+        double* c = C + (long)gi * ldc + gj;
+        *c = (beta == 0.0) ? alpha * acc[a][b][v] : alpha * acc[a][b][v] + beta * (*c);
+      }
     }
-  }
 }
 
 __global__ void kkt_form_kernel(int n, const double* __restrict__ P, const double* __restrict__ Gw, double sigma,
@@ -112,37 +154,34 @@ __global__ void kkt_form_kernel(int n, const double* __restrict__ P, const doubl
 // order per matrix. work: gj_work(n) doubles per matrix (pivot inverse, row panel, old column panel).
 __host__ __device__ inline long gj_work(int n) { return SB * SB + 2L * SB * n; }
 
-// Inverse of the pivot block (bb x bb, bb <= 32) by unblocked Gauss-Jordan in LDS.
+// Inverse of the pivot block (bb x bb, bb <= 32) by unblocked Gauss-Jordan. 32 serial steps: every
+// step reads one copy of the block in LDS and writes the other (one barrier), and the pivot row's
+// quotients, which every thread needs one of, are formed by each thread for its column.
 __global__ void __launch_bounds__(1024) gj_diag_kernel(const double* __restrict__ M, int n, int pb, int bb,
                                                        double* __restrict__ Pinv, int* __restrict__ info) {
   M += blockIdx.z * (long)n * n;
   Pinv += blockIdx.z * gj_work(n);
-  __shared__ double S[SB][SB + 1];
+  __shared__ double S[2][SB][SB + 1];
   const int r = threadIdx.x / SB, c = threadIdx.x % SB;
   const bool act = r < bb && c < bb;
-  S[r][c] = act ? M[(long)(pb + r) * n + pb + c] : 0.0;
+  double src = act ? M[(long)(pb + r) * n + pb + c] : 0.0;
+  S[0][r][c] = src;
   __syncthreads();
   for (int k = 0; k < bb; ++k) {
-    double piv = S[k][k];
+    const double(*const So)[SB + 1] = S[k & 1];
+    double piv = So[k][k];
+    const double srk = So[r][k], skc = So[k][c];
     if (!(piv > 0.0)) {
       if (threadIdx.x == 0) *info = 1;
       piv = 1.0;  // keep the arithmetic finite; the caller reports the failure
     }
-    double srk = S[r][k], skc = S[k][c], src = S[r][c];
-    __syncthreads();
-    double v;
-    if (r == k && c == k)
-      v = 1.0 / piv;
-    else if (r == k)
-      v = skc / piv;
-    else if (c == k)
-      v = -srk / piv;
-    else
-      v = src - srk * (skc / piv);
-    if (act) S[r][c] = v;
+    // the one division of this element: 1 / piv, skc / piv or srk / piv
+    const double quot = (r == k && c == k ? 1.0 : c == k ? -srk : skc) / piv;
+    if (act) src = r == k || c == k ? quot : src - srk * quot;
+    S[(k & 1) ^ 1][r][c] = src;
     __syncthreads();
   }
-  Pinv[r * SB + c] = act ? S[r][c] : 0.0;
+  Pinv[r * SB + c] = act ? src : 0.0;
 }
 
 // Row panel R = Pinv * M[pb:pb+bb, :] (bb x n) and a copy of the old column panel
@@ -181,7 +220,9 @@ __global__ void __launch_bounds__(256) gj_panel_kernel(const double* __restrict_
   }
 }
 
-// Trailing update of one Gauss-Jordan step on a 64 x 64 tile of M.
+// Trailing update of one Gauss-Jordan step on a 64 x 64 tile of M: M - Cold R outside the pivot rows and
+// columns, R in the pivot rows, -Cold Pinv in the pivot columns (the tile's B operand takes Pinv's
+// columns there), Pinv in the pivot block.
 __global__ void __launch_bounds__(256) gj_update_kernel(double* __restrict__ M, int n, int pb, int bb,
                                                         const double* __restrict__ Pinv, const double* __restrict__ R,
                                                         const double* __restrict__ Cold) {
@@ -189,52 +230,52 @@ __global__ void __launch_bounds__(256) gj_update_kernel(double* __restrict__ M, 
   Pinv += blockIdx.z * gj_work(n);
   R += blockIdx.z * gj_work(n);
   Cold += blockIdx.z * gj_work(n);
-  __shared__ double Cs[SB][GT + 1];  // Cs[t][i] = Cold[i0 + i][t]
-  __shared__ double Rs[SB][GT + 1];  // Rs[t][j] = R[t][j0 + j]
-  __shared__ double Ps[SB][SB + 1];
+  __shared__ double Cs[SB][GP];  // Cs[t][i] = Cold[i0 + i][t]
+  __shared__ double Bs[SB][GP];  // Bs[t][j] = R[t][j0 + j], or Pinv[t][j0 + j - pb] in the pivot columns
   const int tid = threadIdx.x;
-  const int tx = tid % 16, ty = tid / 16;
   const int i0 = blockIdx.y * GT, j0 = blockIdx.x * GT;
-  for (int e = tid; e < SB * SB; e += 256) Ps[e / SB][e % SB] = Pinv[e];
   for (int e = tid; e < GT * SB; e += 256) {
-    int i = e / SB, t = e % SB;
-    int gi = i0 + i;
+    const int i = e / SB, t = e % SB, gi = i0 + i;
     Cs[t][i] = (gi < n) ? Cold[(long)gi * SB + t] : 0.0;
   }
   for (int e = tid; e < SB * GT; e += 256) {
-    int t = e / GT, j = e % GT;
-    int gj = j0 + j;
-    Rs[t][j] = (t < bb && gj < n) ? R[(long)t * n + gj] : 0.0;
+    const int t = e / GT, j = e % GT, gj = j0 + j;
+    const bool in_j = gj >= pb && gj < pb + bb;
+    Bs[t][j] = (t < bb && gj < n) ? (in_j ? Pinv[t * SB + gj - pb] : R[(long)t * n + gj]) : 0.0;
   }
+  // the tile's elements of M, loaded before the products
+  double old[2][2][4];
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+#pragma unroll
+      for (int b = 0; b < 2; ++b) {
+        const int gi = i0 + tile_row(a, v), gj = j0 + tile_col(b);
+        old[a][b][v] = gi < n && gj < n ? M[(long)gi * n + gj] : 0.0;
+      }
   __syncthreads();
+  doublex4 acc[2][2];
 #pragma unroll
-  for (int a = 0; a < 4; ++a) {
-    int ii = ty + 16 * a;
-    int gi = i0 + ii;
-    if (gi >= n) continue;
-    bool in_i = gi >= pb && gi < pb + bb;
+  for (int a = 0; a < 2; ++a)
 #pragma unroll
-    for (int b = 0; b < 4; ++b) {
-      int jj = tx + 16 * b;
-      int gj = j0 + jj;
-      if (gj >= n) continue;
-      bool in_j = gj >= pb && gj < pb + bb;
-      double* mp = M + (long)gi * n + gj;
-      if (in_i && in_j) {
-        *mp = Ps[gi - pb][gj - pb];
-      } else if (in_i) {
-        *mp = Rs[gi - pb][jj];
-      } else if (in_j) {
-        double s = 0.0;
-        for (int t = 0; t < bb; ++t) s = fma(Cs[t][ii], Ps[t][gj - pb], s);
-        *mp = -s;
-      } else {
-        double s = 0.0;
-        for (int t = 0; t < bb; ++t) s = fma(Cs[t][ii], Rs[t][jj], s);
-        *mp -= s;
+    for (int b = 0; b < 2; ++b) acc[a][b] = doublex4{0.0, 0.0, 0.0, 0.0};
+  mfma_tile<SB>(Cs, Bs, acc);
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int gi = i0 + tile_row(a, v);
+      if (gi >= n) continue;
+      const bool in_i = gi >= pb && gi < pb + bb;
+#pragma unroll
+      for (int b = 0; b < 2; ++b) {
+        const int gj = j0 + tile_col(b);
+        if (gj >= n) continue;
+        const bool in_j = gj >= pb && gj < pb + bb;
+        M[(long)gi * n + gj] = in_i ? Bs[gi - pb][tile_col(b)] : (in_j ? -acc[a][b][v] : old[a][b][v] - acc[a][b][v]);
       }
     }
-  }
 }
 
 __global__ void symmetrize_kernel(int n, double* __restrict__ M) {
@@ -383,7 +424,7 @@ hipError_t gemm_f64(int M, int N, int K, double alpha, const double* A, long a_r
                     const double* B, long b_rs, long b_cs, double beta, double* C, long ldc, hipStream_t st, int count,
                     long a_bs, long b_bs, long c_bs) {
   if (M <= 0 || N <= 0 || count <= 0) return hipSuccess;
-  dim3 grid((N + GT - 1) / GT, (M + GT - 1) / GT, count);
+  const dim3 grid((N + GT - 1) / GT, (M + GT - 1) / GT, count);
   hipLaunchKernelGGL(gemm_f64_kernel, grid, dim3(256), 0, st, M, N, K, alpha, A, a_rs, a_cs, kscale, B, b_rs, b_cs,
                      beta, C, ldc, a_bs, b_bs, c_bs);
   return hipGetLastError();
