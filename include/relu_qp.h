@@ -247,7 +247,8 @@ int relu_qp_admit(relu_qp_handle* h, const int* slots, int n_slots, int src_slot
 int relu_qp_step(relu_qp_handle* h, int n_checks, void* stream, relu_qp_result* out);
 
 /* Tile shape of the batched engine's GEMM: 128, 64 or 256 matrix rows per tile (x 128 instances);
- * with 128 or 256, the last that many rows of the layer go in tiles of half the rows, run last.
+ * with 128 or 256, the last that many rows of the layer go in tiles of half the rows, run last; with
+ * 64, the layer goes in 32-row tiles while every one of them gets a compute unit.
  * relu_qp_setup of a batched handle runs an autotuner: every shape runs two check intervals of
  * all slots on the handle's own data, timed on the device, and the fastest is kept, where a
  * shape later in the order 128, 64, 256 must be more than 1 % faster than an earlier one (slots

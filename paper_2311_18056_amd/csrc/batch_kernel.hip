@@ -47,6 +47,7 @@ constexpr int BS = kBatchBlock;
 constexpr int TM = kTileM, TN = kTileN, TK = kTileK;
 constexpr int PADB = 8;  // bf16 row padding in LDS (elements)
 constexpr int PADF = 4;  // fp32 row padding in LDS (elements)
+constexpr int kEarlyBlocks = 2;  // accumulator blocks per wave whose state is loaded before the products
 constexpr unsigned kBarSpin = 1u << 24;
 
 enum { ST_RUNNING = 0, ST_SOLVED = 1, ST_MAX_ITER = 2, ST_NONFINITE = 3, ST_ABORTED = 4, ST_INTERNAL = 5 };
@@ -64,7 +65,9 @@ enum { N_RP = 0, N_RD, N_AX, N_Z, N_PX, N_ATY, N_Q };
 // now), one of 4096 instances at n = m = 1600 took 537 us (331 now; all BF16x3).
 // Returns false if a wait exceeded the spin bound or another workgroup gave up (bar[1] set);
 // every workgroup then leaves the kernel.
-__device__ __forceinline__ bool grid_barrier(unsigned* bar, unsigned e) {
+// acquire = false: the caller reads what other workgroups wrote with agent-scope reads only, so the L2
+// keeps its lines (the invalidate takes 2 us, and the weights come from memory again after it).
+__device__ __forceinline__ bool grid_barrier(unsigned* bar, unsigned e, bool acquire = true) {
   __shared__ int ok_s;
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
   asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");  // this wave's stores have left the CU
@@ -90,7 +93,7 @@ __device__ __forceinline__ bool grid_barrier(unsigned* bar, unsigned e) {
       }
       __builtin_amdgcn_s_sleep(1);
     }
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    if (acquire) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     if (lane == 0) ok_s = ok;
   }
   __syncthreads();
@@ -163,16 +166,19 @@ __device__ __forceinline__ int swz(int r) {
   else
     return r & 15;
 }
-// ROWS rows of one K block starting at byte address src (rows CPR * 16 bytes apart) to lds.
-template <int ROWS, int CPR>
+// ROWS rows of one K block starting at byte address src (rows CPR * 16 bytes apart) to lds; with PANEL,
+// several panels of PANEL rows each, src being the caller's wave's panel.
+// AUX: cache policy of the reads (kAgentScope: past this XCD's L2, which may hold older data).
+constexpr int kAgentScope = 16;
+template <int ROWS, int CPR, int PANEL = ROWS, int AUX = 0>
 __device__ __forceinline__ void dma_panel(const unsigned char* src, unsigned char* lds, int wave) {
   static_assert(ROWS * CPR % BS == 0, "a panel is a whole number of wave instructions per thread");
 #pragma unroll
   for (int i = 0; i < ROWS * CPR / BS; ++i) {
     // instruction i covers rows [i BS / CPR, (i + 1) BS / CPR): a uniform base plus a lane offset
-    const int ci = i * BS + threadIdx.x, row = ci / CPR, c = (ci % CPR) ^ swz<CPR>(row);
+    const int ci = i * BS + threadIdx.x, row = ci / CPR % PANEL, c = (ci % CPR) ^ swz<CPR>(row);
     const unsigned off = (unsigned)((row - i * (BS / CPR)) * (CPR * 16) + c * 16);
-    __builtin_amdgcn_global_load_lds(src + i * BS * 16 + off, (lds_ptr_t)(lds + i * BS * 16 + wave * 1024), 16, 0, 0);
+    __builtin_amdgcn_global_load_lds(src + i * BS * 16 + off, (lds_ptr_t)(lds + i * BS * 16 + wave * 1024), 16, 0, AUX);
   }
 }
 template <int CPR>
@@ -185,6 +191,18 @@ template <int N>
 __device__ __forceinline__ void wait_vm() {
   static_assert(N >= 0 && N < 64, "vmcnt range");
   __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
+}
+// Waits until at most LOADS * ahead are outstanding, ahead <= N.
+template <int N, int LOADS>
+__device__ __forceinline__ void wait_stages(int ahead) {
+  if constexpr (N == 0) {
+    wait_vm<0>();
+  } else {
+    if (ahead >= N)
+      wait_vm<LOADS * N>();
+    else
+      wait_stages<N - 1, LOADS>(ahead);
+  }
 }
 // Workgroup barrier that the compiler does not move memory operations across.
 __device__ __forceinline__ void lds_barrier() {
@@ -202,19 +220,13 @@ __device__ __forceinline__ void lds_barrier() {
 // every copy but the last k stages' has landed. Loads of the caller must be complete on entry.
 template <int NST, int LOADS, typename Issue, typename Comp>
 __device__ __forceinline__ void kloop(int s0, int s1, unsigned char* lds, int stage_bytes, Issue&& issue, Comp&& comp) {
-  static_assert(NST >= 2 && NST <= 4 && LOADS * (NST - 2) < 64, "pipeline depth");
+  static_assert(NST >= 2 && LOADS * (NST - 2) < 64, "pipeline depth");
   lds_barrier();
 #pragma unroll
   for (int p = 0; p < NST - 1; ++p)
     if (s0 + p < s1) issue(s0 + p, lds + p * stage_bytes);
   for (int s = s0; s < s1; ++s) {
-    const int ahead = min(s1 - 1 - s, NST - 2);  // stages issued after s
-    if (NST >= 4 && ahead >= 2)
-      wait_vm<LOADS*(NST >= 4 ? 2 : 0)>();
-    else if (NST >= 3 && ahead >= 1)
-      wait_vm<LOADS*(NST >= 3 ? 1 : 0)>();
-    else
-      wait_vm<0>();
+    wait_stages<NST - 2, LOADS>(min(s1 - 1 - s, NST - 2));  // all but the stages issued after s
     lds_barrier();
     const int q = s - s0;
     if (s + NST - 1 < s1) issue(s + NST - 1, lds + ((q + NST - 1) % NST) * stage_bytes);
@@ -223,34 +235,44 @@ __device__ __forceinline__ void kloop(int s0, int s1, unsigned char* lds, int st
 }
 
 // ------------------------------------------------------------------------------------------
-// Layer GEMM tile: TM instances (list positions) x TNV matrix rows (256, 128 or 64), four waves
-// in a 2 x 2 grid, each owning 64 instances x TNV/2 rows as 2 x BJ blocks of 32 x 32
-// accumulators (lane layout of v_mfma_f32_32x32x*). A stage holds the A rows (instances) then
-// the B rows (matrix rows): BF16 high and low panels of 64-byte rows, or FP32 panels of 128-byte
-// rows, (TM + TNV) x 128 bytes in both cases. A larger tile reads fewer LDS bytes per product
-// and fewer operand bytes per flop; which wins depends on how many tiles a problem has (the
-// autotuner).
+// Layer GEMM tile: TM instances (list positions) x TNV matrix rows, four waves. 256, 128 or 64 rows: a
+// 2 x 2 grid of waves, each owning 64 instances x TNV/2 rows as 2 x BJ blocks of 32 x 32 accumulators
+// (lane layout of v_mfma_f32_32x32x*); 32 rows: each wave owns 32 instances x 32 rows, one block. A
+// stage holds the A rows (instances) then the B rows (matrix rows): BF16 high and low panels of 64-byte
+// rows, or FP32 panels of 128-byte rows, (TM + TNV) x 128 bytes in both cases. A larger tile reads fewer
+// LDS bytes per product and fewer operand bytes per flop; which wins depends on how many tiles a problem
+// has (the autotuner). An element's products and their order are the same in every shape. The ring takes
+// the LDS there is: a short K loop of few tiles is bound by the latency of its first stages.
 template <int TNV>
 struct LayerGeo {
-  static constexpr int BJ = TNV / 64;
+  static constexpr int NI = TNV >= 64 ? 2 : 1;        // blocks per wave: instances
+  static constexpr int BJ = TNV >= 64 ? TNV / 64 : 1;  // and rows
   static constexpr int STAGE = (TM + TNV) * 128;
   static constexpr int LOADS = STAGE / 16 / BS;
-  static constexpr int NST = TNV >= 256 ? 3 : 4;
+  static constexpr int NST = TNV >= 256 ? 3 : TNV >= 128 ? 4 : TNV >= 64 ? 6 : 7;
   static constexpr size_t SMEM = (size_t)NST * STAGE;
+  // first instance and first row of this wave's part of the tile
+  static __device__ __forceinline__ int inst0(int wave) { return TNV >= 64 ? wave / 2 * 64 : wave * 32; }
+  static __device__ __forceinline__ int row0(int wave) { return TNV >= 64 ? wave % 2 * (TNV / 2) : 0; }
 };
 
-template <int PREC, int TNV>
+template <int PREC, int TNV, int AUX>
 __device__ __forceinline__ void layer_issue(const void* Aa, const void* Ab, const void* Ba, const void* Bb, long arow,
                                             long brow, long as, long bs, int s, unsigned char* buf, int wave) {
   if constexpr (PREC == kBatchBF16x3) {
     const long ao = ((long)s * as + arow * TK) * 2, bo = ((long)s * bs + brow * TK) * 2;
-    dma_panel<TM, 4>(static_cast<const unsigned char*>(Aa) + ao, buf, wave);
-    dma_panel<TM, 4>(static_cast<const unsigned char*>(Ab) + ao, buf + TM * 64, wave);
-    dma_panel<TNV, 4>(static_cast<const unsigned char*>(Ba) + bo, buf + TM * 128, wave);
-    dma_panel<TNV, 4>(static_cast<const unsigned char*>(Bb) + bo, buf + TM * 128 + TNV * 64, wave);
+    dma_panel<TM, 4, TM, AUX>(static_cast<const unsigned char*>(Aa) + ao, buf, wave);
+    dma_panel<TM, 4, TM, AUX>(static_cast<const unsigned char*>(Ab) + ao, buf + TM * 64, wave);
+    if constexpr (TNV * 4 >= BS) {
+      dma_panel<TNV, 4>(static_cast<const unsigned char*>(Ba) + bo, buf + TM * 128, wave);
+      dma_panel<TNV, 4>(static_cast<const unsigned char*>(Bb) + bo, buf + TM * 128 + TNV * 64, wave);
+    } else {  // 32 rows: two waves copy each panel (the panels lie one after the other)
+      static_assert(TNV * 8 == BS, "one instruction per wave for both panels");
+      dma_panel<2 * TNV, 4, TNV>(static_cast<const unsigned char*>(wave < 2 ? Ba : Bb) + bo, buf + TM * 128, wave);
+    }
   } else {
     const long ao = ((long)s * as + arow * TK) * 4, bo = ((long)s * bs + brow * TK) * 4;
-    dma_panel<TM, 8>(static_cast<const unsigned char*>(Aa) + ao, buf, wave);
+    dma_panel<TM, 8, TM, AUX>(static_cast<const unsigned char*>(Aa) + ao, buf, wave);
     dma_panel<TNV, 8>(static_cast<const unsigned char*>(Ba) + bo, buf + TM * 128, wave);
   }
 }
@@ -261,30 +283,31 @@ __device__ __forceinline__ void layer_issue(const void* Aa, const void* Ab, cons
 // pair (2 g + l / 32) as four floats and feeds component s to the s-th of four 32x32x2
 // products; A and B read the same chunks, so every product pairs equal k.
 template <int PREC, int TNV>
-__device__ __forceinline__ void layer_comp(const unsigned char* buf, floatx16 (&acc)[2][TNV / 64]) {
-  constexpr int BJ = TNV / 64;
+__device__ __forceinline__ void layer_comp(const unsigned char* buf,
+                                           floatx16 (&acc)[LayerGeo<TNV>::NI][LayerGeo<TNV>::BJ]) {
+  constexpr int NI = LayerGeo<TNV>::NI, BJ = LayerGeo<TNV>::BJ;
   const int lane = threadIdx.x % 64, wave = threadIdx.x / 64;
-  const int wm = wave / 2, wn = wave % 2;
+  const int a0 = LayerGeo<TNV>::inst0(wave) + lane % 32, b0 = LayerGeo<TNV>::row0(wave) + lane % 32;
   if constexpr (PREC == kBatchBF16x3) {
     const unsigned char *ah = buf, *al = buf + TM * 64, *bh = buf + TM * 128, *bl = buf + TM * 128 + TNV * 64;
 #pragma unroll
     for (int kk = 0; kk < 2; ++kk) {
       const int c = 2 * kk + lane / 32;
-      bf16x8 fa[2][2], fb[BJ][2];
+      bf16x8 fa[NI][2], fb[BJ][2];
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const int r = wm * 64 + i * 32 + lane % 32;
+      for (int i = 0; i < NI; ++i) {
+        const int r = a0 + i * 32;
         fa[i][0] = *reinterpret_cast<const bf16x8*>(frag_at<4>(ah, r, c));
         fa[i][1] = *reinterpret_cast<const bf16x8*>(frag_at<4>(al, r, c));
       }
 #pragma unroll
       for (int j = 0; j < BJ; ++j) {
-        const int r = wn * (TNV / 2) + j * 32 + lane % 32;
+        const int r = b0 + j * 32;
         fb[j][0] = *reinterpret_cast<const bf16x8*>(frag_at<4>(bh, r, c));
         fb[j][1] = *reinterpret_cast<const bf16x8*>(frag_at<4>(bl, r, c));
       }
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+      for (int i = 0; i < NI; ++i)
 #pragma unroll
         for (int j = 0; j < BJ; ++j) {
           acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i][0], fb[j][0], acc[i][j], 0, 0, 0);
@@ -297,16 +320,16 @@ __device__ __forceinline__ void layer_comp(const unsigned char* buf, floatx16 (&
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
       const int c = 2 * g + lane / 32;
-      floatx4 fa[2], fb[BJ];
+      floatx4 fa[NI], fb[BJ];
 #pragma unroll
-      for (int i = 0; i < 2; ++i) fa[i] = *reinterpret_cast<const floatx4*>(frag_at<8>(pa, wm * 64 + i * 32 + lane % 32, c));
+      for (int i = 0; i < NI; ++i) fa[i] = *reinterpret_cast<const floatx4*>(frag_at<8>(pa, a0 + i * 32, c));
 #pragma unroll
       for (int j = 0; j < BJ; ++j)
-        fb[j] = *reinterpret_cast<const floatx4*>(frag_at<8>(pb, wn * (TNV / 2) + j * 32 + lane % 32, c));
+        fb[j] = *reinterpret_cast<const floatx4*>(frag_at<8>(pb, b0 + j * 32, c));
 #pragma unroll
       for (int s = 0; s < 4; ++s)
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+        for (int i = 0; i < NI; ++i)
 #pragma unroll
           for (int j = 0; j < BJ; ++j)
             acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[i][s], fb[j][s], acc[i][j], 0, 0, 0);
@@ -316,29 +339,30 @@ __device__ __forceinline__ void layer_comp(const unsigned char* buf, floatx16 (&
 
 // acc = sum over k in [0, L) of V[row][k] W[col][k] for the tile whose operand rows start at
 // list position arow and matrix rows at brow; V and W are zero past column L.
-template <int PREC, int TNV>
+template <int PREC, int TNV, int AUX>
 __device__ __forceinline__ void layer_tile(unsigned char* lds, const void* Aa, const void* Ab, const void* Ba,
                                            const void* Bb, long arow, long brow, long as, long bs, int L,
-                                           floatx16 (&acc)[2][TNV / 64]) {
+                                           floatx16 (&acc)[LayerGeo<TNV>::NI][LayerGeo<TNV>::BJ]) {
   using G = LayerGeo<TNV>;
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < G::NI; ++i)
 #pragma unroll
     for (int j = 0; j < G::BJ; ++j) acc[i][j] = floatx16{};
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
   kloop<G::NST, G::LOADS>(
       0, (L + TK - 1) / TK, lds, G::STAGE,
-      [&](int s, unsigned char* buf) { layer_issue<PREC, TNV>(Aa, Ab, Ba, Bb, arow, brow, as, bs, s, buf, wave); },
+      [&](int s, unsigned char* buf) { layer_issue<PREC, TNV, AUX>(Aa, Ab, Ba, Bb, arow, brow, as, bs, s, buf, wave); },
       [&](int, const unsigned char* buf) { layer_comp<PREC, TNV>(buf, acc); });
 }
 
 // Position in the tile of accumulator element v of block (i, j) for this lane.
-__device__ __forceinline__ int acc_row(int wm, int i, int v, int lane) {
-  return wm * 64 + i * 32 + 8 * (v / 4) + 4 * (lane / 32) + (v % 4);
+template <int TNV>
+__device__ __forceinline__ int acc_row(int i, int v, int lane) {
+  return LayerGeo<TNV>::inst0(threadIdx.x / 64) + i * 32 + 8 * (v / 4) + 4 * (lane / 32) + (v % 4);
 }
 template <int TNV>
-__device__ __forceinline__ int acc_col(int wn, int j, int lane) {
-  return wn * (TNV / 2) + j * 32 + lane % 32;
+__device__ __forceinline__ int acc_col(int j, int lane) {
+  return LayerGeo<TNV>::row0(threadIdx.x / 64) + j * 32 + lane % 32;
 }
 
 // ------------------------------------------------------------------------------------------
@@ -583,6 +607,10 @@ __global__ void __launch_bounds__(BS) batch_kernel(BatchArgs a_in) {
   unsigned char* const lds = smem_raw;  // operand stages of the layer and check GEMMs
   __shared__ int s_count[64];
   __shared__ int s_list[TM];   // instance ids of the current M tile
+  // descriptors and instance ids of this workgroup's first layer tiles: they only change at a check
+  constexpr int kKeep = 4;
+  __shared__ MTile s_mt[kKeep], s_mtx;
+  __shared__ int s_lists[kKeep][TM];
   __shared__ float s_rho[64];  // grid penalties in FP32
   const int tid = threadIdx.x, lane = tid % 64, wave = tid / 64;
   const int wm = wave / 2, wn = wave % 2;
@@ -601,7 +629,6 @@ __global__ void __launch_bounds__(BS) batch_kernel(BatchArgs a_in) {
   // round of 256 workgroups). Which rows a tile shape covers depends only on L and TNV, so an
   // instance's arithmetic is the same alone and in any batch.
   constexpr int TNS = TNV >= 128 ? TNV / 2 : TNV;
-  static_assert(LayerGeo<TNS>::SMEM <= LayerGeo<TNV>::SMEM, "the small row tiles fit the large ones' LDS");
   const int nbig = TNV >= 128 ? (L - 1) / TNV : (L + TNV - 1) / TNV;
   const int ntiles_n = nbig + (L - nbig * TNV + TNS - 1) / TNS;
   const float alpha = (float)a.alpha, oma = (float)(1.0 - a.alpha), sigma = (float)a.sigma;
@@ -702,92 +729,133 @@ __global__ void __launch_bounds__(BS) batch_kernel(BatchArgs a_in) {
   if (!grid_barrier(a.bar, ++epoch)) return;
 
   const int ci = a.check_interval;
+  // this segment's tiles (from one check to the next the M tiles stay the same). With so few tiles that
+  // 32-row ones still get a compute unit each, the layer goes in 32-row tiles (64-row kernel only): 333
+  // instances of n = m = 800 in FP32 are 75 tiles of 64 rows or 150 of 32
+  int nmt = 0;
+  bool fine = false;
+  TileWalk tw(0, 0, 0);
+  auto start_segment = [&]() __attribute__((always_inline)) {
+    const auto& a = *fresh(kp);
+    nmt = a.mtiles[0];
+    const MTile* const mts = reinterpret_cast<const MTile*>(a.mtiles + 1);
+    const int fine_n = (L + 31) / 32;
+    fine = TNV == 64 && nmt * fine_n <= G;
+    tw = TileWalk(nmt, 0, fine ? fine_n : ntiles_n, true);
+    __syncthreads();  // the previous segment is done with s_mt and s_lists
+    for (int i = 0, t = tw.first(); i < kKeep && t < tw.count; ++i, t += tw.per) {
+      const MTile mt = mts[tw.mt(t)];
+      if (tid == 0) s_mt[i] = mt;
+      if (tid < TM) s_lists[i][tid] = a.lists[mt.off + (tid < mt.cnt ? tid : 0)];
+    }
+    __syncthreads();
+  };
+  start_segment();
   for (int k = 1; k <= a.steps; ++k) {
     const auto& a = *fresh(kp);
     const bool is_check = (k % ci == 0) || (k == a.steps);
-    const int nmt = a.mtiles[0];
     const MTile* mts = reinterpret_cast<const MTile*>(a.mtiles + 1);
     const long vin = (long)(k & 1) * vpar, vout = (long)((k + 1) & 1) * vpar;
-    const TileWalk tw(nmt, 0, ntiles_n, true);
 
-    // ---- layer GEMM + fused update: one tile of TR rows starting at matrix row r0
-    auto layer_step = [&](auto TRc, int mti, int r0) __attribute__((always_inline)) {
-      constexpr int TR = decltype(TRc)::value, BJR = TR / 64;
+    // ---- layer GEMM + fused update: one tile of TR rows starting at matrix row r0, its descriptor and
+    // instance ids in LDS
+    auto layer_step = [&](auto TRc, const MTile& mt_l, const int* list, int r0) __attribute__((always_inline)) {
+      constexpr int TR = decltype(TRc)::value, NI = LayerGeo<TR>::NI, BJ = LayerGeo<TR>::BJ;
+      // the state of a wave's elements is loaded before the products where registers allow (64 per block)
+      constexpr bool EARLY = NI * BJ <= kEarlyBlocks;
       const auto& a = *fresh(kp);
-      const MTile mt = mts[mti];
-      load_list(a.lists, mt);
+      MTile mt;
+      mt.j = __builtin_amdgcn_readfirstlane(mt_l.j);
+      mt.off = __builtin_amdgcn_readfirstlane(mt_l.off);
+      mt.cnt = __builtin_amdgcn_readfirstlane(mt_l.cnt);
       constexpr long es = PREC == kBatchBF16x3 ? 2 : 4;
       const unsigned char* Aa = static_cast<const unsigned char*>(a.Va) + vin * es;
       const unsigned char* Ab = a.Vb ? static_cast<const unsigned char*>(a.Vb) + vin * es : nullptr;
       const unsigned char* Ba = static_cast<const unsigned char*>(a.Wa) + (long)mt.j * a.w_stride * es;
       const unsigned char* Bb = a.Wb ? static_cast<const unsigned char*>(a.Wb) + (long)mt.j * a.w_stride * es : nullptr;
-      floatx16 acc[2][BJR];
-      layer_tile<PREC, TR>(lds, Aa, Ab, Ba, Bb, mt.off, (long)r0, as, bs, L, acc);
+      // A lane's 16 elements of a block share its column r (one layer row) and take 16 instances. Elements
+      // past the tile's instance count load valid rows (the list repeats its first id) and store nothing;
+      // rows past L load row L - 1 and store nothing. Offsets are 32-bit (B * max(n, m) and the operand
+      // size, in bytes, are checked at setup).
+      float st[EARLY ? NI : 1][EARLY ? BJ : 1][4][16];  // x, q or z, y, l, u
+      auto load_state = [&](auto I, auto J, float(&o)[4][16]) __attribute__((always_inline)) {
+        const auto& ae = *fresh(kp);
+        const int rr = r0 + acc_col<TR>(decltype(J)::value, lane), r = rr < L ? rr : L - 1;
+        const bool xr = r < n;
+        const unsigned per = xr ? n : m, col = xr ? r : r - n;
+        const float* const p0 = xr ? ae.X : ae.Z;
+        const float* const p1 = xr ? ae.Q : ae.Y;
+        unsigned e[16];
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          e[v] = (unsigned)list[acc_row<TR>(decltype(I)::value, v, lane)] * per + col;
+          o[0][v] = at32(p0, e[v]);
+          o[1][v] = at32(p1, e[v]);
+        }
+        if (!xr) {
+#pragma unroll
+          for (int v = 0; v < 16; ++v) {
+            o[2][v] = at32(ae.Lo, e[v]);
+            o[3][v] = at32(ae.Up, e[v]);
+          }
+        }
+      };
+      if constexpr (EARLY)
+        static_for<0, NI>([&](auto I) {
+          static_for<0, BJ>([&](auto J) { load_state(I, J, st[decltype(I)::value][decltype(J)::value]); });
+        });
+      floatx16 acc[NI][BJ];
+      layer_tile<PREC, TR, TR == 32 ? kAgentScope : 0>(lds, Aa, Ab, Ba, Bb, mt.off, (long)r0, as, bs, L, acc);
       const float rho_bar = s_rho[mt.j];
       // epilogue, one 32 x 32 block at a time (block indices are compile-time constants, so the
-      // accumulators stay in registers). A lane's 16 elements of a block share its column r (one
-      // layer row) and take 16 instances; the instances' state offsets are formed once per
-      // block row i. All state loads of a block are issued together, then the row-local update
-      // (relaxation, clamp, dual) and the stores; elements past the tile's instance count load
-      // valid rows (the list repeats its first id) and store nothing. Offsets are 32-bit
-      // (B * max(n, m) and the operand size, in bytes, are checked at setup).
+      // accumulators stay in registers): the row-local update (relaxation, clamp, dual) and the stores
       const auto& ae = *fresh(kp);
       unsigned char* const vo = static_cast<unsigned char*>(ae.Va) + vout * (PREC == kBatchBF16x3 ? 2 : 4);
       unsigned char* const vo2 = ae.Vb ? static_cast<unsigned char*>(ae.Vb) + vout * 2 : nullptr;
-      static_for<0, 2>([&](auto I) {
+      static_for<0, NI>([&](auto I) {
         constexpr int i = decltype(I)::value;
         unsigned on[16], om[16], oo[16];
         bool ok[16];
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
-          const int ti = acc_row(wm, i, v, lane);
-          const unsigned b = (unsigned)s_list[ti];
+          const int ti = acc_row<TR>(i, v, lane);
+          const unsigned b = (unsigned)list[ti];
           on[v] = b * (unsigned)n;
           om[v] = b * (unsigned)m;
           oo[v] = (unsigned)ti * TK;
           ok[v] = ti < mt.cnt;
         }
-        static_for<0, BJR>([&](auto J) {
+        static_for<0, BJ>([&](auto J) {
           constexpr int j = decltype(J)::value;
-          const int r = r0 + acc_col<TR>(wn, j, lane);
+          const int r = r0 + acc_col<TR>(j, lane);
+          float late[4][16];
+          if constexpr (!EARLY) load_state(I, J, late);
+          const float(&o)[4][16] = EARLY ? st[EARLY ? i : 0][EARLY ? j : 0] : late;
           if (r >= L) return;
           // operand index of element v: obase + oo[v] (K-blocked, list position mt.off + ti)
           const unsigned obase = ((unsigned)(r / TK) * (unsigned)ae.bpad + (unsigned)mt.off) * TK + (unsigned)(r % TK);
           if (r < n) {
             // check operand: x in original units, rounded as the output is
             const double fx = ae.scl ? ae.scl[2 * n + 2 * m + r] : 1.0;
-            float xo[16], qv[16];
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
-              xo[v] = at32(ae.X, on[v] + r);
-              qv[v] = at32(ae.Q, on[v] + r);
-            }
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-              const float x = alpha * acc[i][j][v] + oma * xo[v];
+              const float x = fmaf(alpha, acc[i][j][v], oma * o[0][v]);
               if (!ok[v]) continue;
               at32(ae.X, on[v] + r) = x;
               if (is_check)
                 at32(ae.CVd, obase + oo[v]) = (double)(float)((double)x * fx);
               else
-                put_operand32<PREC>(vo, vo2, obase + oo[v], sigma * x - qv[v]);
+                put_operand32<PREC>(vo, vo2, obase + oo[v], fmaf(sigma, x, -o[1][v]));
             }
           } else {
             const int ri = r - n;
             const float rho = rho_bar * (ae.eq[ri] ? eqs : 1.0f), rinv = 1.0f / rho;
             const double fy = ae.scl ? ae.scl[3 * n + 2 * m + ri] : 1.0;
-            float zo[16], yo[16], lo[16], up[16];
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
-              zo[v] = at32(ae.Z, om[v] + ri);
-              yo[v] = at32(ae.Y, om[v] + ri);
-              lo[v] = at32(ae.Lo, om[v] + ri);
-              up[v] = at32(ae.Up, om[v] + ri);
-            }
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-              const float t2 = alpha * acc[i][j][v] + oma * zo[v] + yo[v] * rinv;
-              const float zn = t2 < lo[v] ? lo[v] : (t2 > up[v] ? up[v] : t2);
+              const float t2 = fmaf(o[1][v], rinv, fmaf(alpha, acc[i][j][v], oma * o[0][v]));
+              const float lo = o[2][v], up = o[3][v];
+              const float zn = t2 < lo ? lo : (t2 > up ? up : t2);
               const float yn = rho * (t2 - zn);
               if (!ok[v]) continue;
               at32(ae.Z, om[v] + ri) = zn;
@@ -795,20 +863,35 @@ __global__ void __launch_bounds__(BS) batch_kernel(BatchArgs a_in) {
               if (is_check)
                 at32(ae.CVd + cvy, obase + oo[v]) = (double)(float)((double)yn * fy);
               else
-                put_operand32<PREC>(vo, vo2, obase + oo[v], rho * zn - yn);
+                put_operand32<PREC>(vo, vo2, obase + oo[v], fmaf(rho, zn, -yn));
             }
           }
         });
       });
     };
-    for (int t = tw.first(); t < tw.count; t += tw.per) {
+    for (int i = 0, t = tw.first(); t < tw.count; ++i, t += tw.per) {
       const int nt = tw.nt(t);
-      if (nt < nbig)
-        layer_step(std::integral_constant<int, TNV>{}, tw.mt(t), nt * TNV);
+      const MTile* mt = &s_mt[i];
+      const int* list = s_lists[i];
+      if (i >= kKeep) {
+        mt = &s_mtx;
+        list = s_list;
+        __syncthreads();  // the previous tile is done with s_mtx and s_list
+        const MTile d = mts[tw.mt(t)];
+        if (tid == 0) s_mtx = d;
+        if (tid < TM) s_list[tid] = a.lists[d.off + (tid < d.cnt ? tid : 0)];
+        __syncthreads();
+      }
+      if (TNV == 64 && fine)
+        layer_step(std::integral_constant<int, 32>{}, *mt, list, nt * 32);
+      else if (nt < nbig)
+        layer_step(std::integral_constant<int, TNV>{}, *mt, list, nt * TNV);
       else
-        layer_step(std::integral_constant<int, TNS>{}, tw.mt(t), nbig * TNV + (nt - nbig) * TNS);
+        layer_step(std::integral_constant<int, TNS>{}, *mt, list, nbig * TNV + (nt - nbig) * TNS);
     }
-    if (!grid_barrier(a.bar, ++epoch)) return;
+    // 32-row tiles read V at agent scope, and everything else an iteration reads is constant in the segment
+    // or written by this workgroup
+    if (!grid_barrier(a.bar, ++epoch, !(TNV == 64 && fine) || is_check)) return;
     if (!is_check) continue;
 
     // ---- check GEMM in FP64: [P, A'; A, 0] [x; y] as three kinds of tiles, each over one K
@@ -987,6 +1070,7 @@ __global__ void __launch_bounds__(BS) batch_kernel(BatchArgs a_in) {
     // ---- next layer input for the instances still running (penalty may have changed)
     layer_input<PREC>(*fresh(kp), s_rho, vout);
     if (!grid_barrier(a.bar, ++epoch)) return;
+    start_segment();
   }
   // slots still running carry their iteration count into the next launch
   for (long b = gtid; b < B; b += gstride)
@@ -995,7 +1079,9 @@ __global__ void __launch_bounds__(BS) batch_kernel(BatchArgs a_in) {
 
 template <int TNV>
 constexpr size_t kernel_smem() {
-  return LayerGeo<TNV>::SMEM > CheckGeo::SMEM ? LayerGeo<TNV>::SMEM : CheckGeo::SMEM;
+  constexpr int small = TNV > 64 ? TNV / 2 : 32;  // the smaller row tiles of the same kernel
+  constexpr size_t layer = LayerGeo<TNV>::SMEM > LayerGeo<small>::SMEM ? LayerGeo<TNV>::SMEM : LayerGeo<small>::SMEM;
+  return layer > CheckGeo::SMEM ? layer : CheckGeo::SMEM;
 }
 
 }  // namespace
