@@ -143,6 +143,30 @@ __device__ __forceinline__ double swap_add(double x, double y) {
          __builtin_bit_cast(double, (uint64_t)yl | ((uint64_t)yh << 32));
 }
 
+// Maximum of the two lanes whose indices differ in bit D (16 or 32), in both.
+template <int D>
+__device__ __forceinline__ uint64_t max_swap(uint64_t v) {
+  const uint32_t lo = (uint32_t)v, hi = (uint32_t)(v >> 32);
+  uint64_t x, y;
+  if constexpr (D == 32) {
+    const auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+    const auto h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+    x = (uint64_t)(uint32_t)l[0] | ((uint64_t)(uint32_t)h[0] << 32);
+    y = (uint64_t)(uint32_t)l[1] | ((uint64_t)(uint32_t)h[1] << 32);
+  } else {
+    const auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+    const auto h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+    x = (uint64_t)(uint32_t)l[0] | ((uint64_t)(uint32_t)h[0] << 32);
+    y = (uint64_t)(uint32_t)l[1] | ((uint64_t)(uint32_t)h[1] << 32);
+  }
+  return x > y ? x : y;
+}
+// Maximum over the lanes with equal lane % 8, in every lane.
+__device__ __forceinline__ uint64_t max_over_groups(uint64_t v) {
+  const uint64_t o = __builtin_bit_cast(uint64_t, dpp_mov<0x128>(__builtin_bit_cast(double, v)));  // lane ^ 8
+  return max_swap<32>(max_swap<16>(o > v ? o : v));
+}
+
 // one step at distance D on C values (C even: pair step; C == 1: plain step)
 template <int D, int C, typename T, int N>
 __device__ __forceinline__ void rr_step(T (&v)[N], int lane) {

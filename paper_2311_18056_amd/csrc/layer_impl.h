@@ -129,30 +129,6 @@ __device__ __forceinline__ bool gather(const uint64_t* buf, int L, int cs, bool 
   return ok;
 }
 
-// Maximum of the two lanes whose indices differ in bit D (16 or 32), in both.
-template <int D>
-__device__ __forceinline__ uint64_t max_swap(uint64_t v) {
-  const uint32_t lo = (uint32_t)v, hi = (uint32_t)(v >> 32);
-  uint64_t x, y;
-  if constexpr (D == 32) {
-    const auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
-    const auto h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
-    x = (uint64_t)(uint32_t)l[0] | ((uint64_t)(uint32_t)h[0] << 32);
-    y = (uint64_t)(uint32_t)l[1] | ((uint64_t)(uint32_t)h[1] << 32);
-  } else {
-    const auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
-    const auto h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
-    x = (uint64_t)(uint32_t)l[0] | ((uint64_t)(uint32_t)h[0] << 32);
-    y = (uint64_t)(uint32_t)l[1] | ((uint64_t)(uint32_t)h[1] << 32);
-  }
-  return x > y ? x : y;
-}
-// Maximum over the lanes with equal lane % 8, in every lane.
-__device__ __forceinline__ uint64_t max_over_groups(uint64_t v) {
-  const uint64_t o = __builtin_bit_cast(uint64_t, dpp_mov<0x128>(__builtin_bit_cast(double, v)));  // lane ^ 8
-  return max_swap<32>(max_swap<16>(o > v ? o : v));
-}
-
 // Poll the 2-word FP64 norm partials of all workgroups (count of them, at most 8 * 256: one per
 // workgroup and norm); mx: the largest of this lane's entries tid and tid + BS, which carry norm
 // tid % 8.

@@ -8,8 +8,7 @@
 namespace rqp {
 
 // Problems with n + m <= kSmallRows rows run on one workgroup of kSmallBlock threads; the
-// layer matrix of the active penalty (at most 128 x 128 entries) sits in registers, at most 16
-// entries per thread.
+// layer matrix of the active penalty (at most 128 x 128 entries) sits in registers.
 constexpr int kSmallRows = 128;
 constexpr int kSmallBlock = 1024;
 
