@@ -247,7 +247,7 @@ int relu_qp_admit(relu_qp_handle* h, const int* slots, int n_slots, int src_slot
 int relu_qp_step(relu_qp_handle* h, int n_checks, void* stream, relu_qp_result* out);
 
 /* Tile shape of the batched engine's GEMM: 128, 64 or 256 matrix rows per tile (x 128 instances);
- * with 128 or 256, the last that many rows of the layer go in tiles of half the rows, run last; with
+ * with 128 (256), the last that many rows of the layer go in tiles of 32 (128) rows, run last; with
  * 64, the layer goes in 32-row tiles while every one of them gets a compute unit.
  * relu_qp_setup of a batched handle runs an autotuner: every shape runs two check intervals of
  * all slots on the handle's own data, timed on the device, and the fastest is kept, where a
@@ -299,8 +299,8 @@ int relu_qp_get_rho_grid(const relu_qp_handle* h, double* grid /* n_rho */, int*
  * n + m <= 128 runs its solves (relu_qp_solve, relu_qp_solve_x0, relu_qp_solve_sequence) on one
  * workgroup with the layer matrix in registers; larger problems run the persistent kernel on
  * about one workgroup per 12.5 rows (fewer when a workgroup holds fewer rows on chip, at most
- * one per compute unit), and closed loops and Ruiz-scaled problems on one workgroup per compute
- * unit (at most one per row).
+ * one per compute unit), and closed loops and Ruiz-scaled problems on about one workgroup per
+ * 8 rows (at most one per compute unit).
  * A grid > 0 makes every solve use the persistent kernel on that many workgroups; it must lie
  * in [ceil((n+m)/64), min(n+m, the cooperative limit)]. relu_qp_get_launch reports the grid of
  * plain solves (1 for the single-workgroup kernel) and the workgroup size. */

@@ -429,6 +429,12 @@ __device__ __forceinline__ void check_tile(unsigned char* lds, const double* A, 
 __device__ __forceinline__ int acc64_row(int wm, int i, int v, int lane) { return wm * 64 + i * 16 + lane / 16 + 4 * v; }
 __device__ __forceinline__ int acc64_col(int wn, int j, int lane) { return wn * 64 + j * 16 + lane % 16; }
 
+// Rows of the tiles that take the last TNV rows of the layer.
+template <int TNV>
+constexpr int small_rows() {
+  return TNV >= 256 ? 128 : TNV >= 128 ? 32 : 64;
+}
+
 // M-tile descriptor: {penalty index, offset into lists, instance count}
 struct MTile {
   int j, off, cnt;
@@ -623,12 +629,13 @@ __global__ void __launch_bounds__(BS) batch_kernel(BatchArgs a_in) {
   const long as = a.bpad * TK, bs = a.lpad * TK, cs = a.cpad * TK;
   const int NX = (n + T64 - 1) / T64, NC = (m + T64 - 1) / T64;  // check row tiles: x rows, constraint rows
   // Row tiles of the layer GEMM: TNV rows each, except that the last TNV rows (or fewer) go in
-  // tiles of TNS = TNV / 2 rows. The walks take row tiles in increasing order, so these come in
-  // the last round of workgroups, which otherwise costs a whole round of TNV-row tiles however
-  // few of them it holds (4096 instances x 3200 rows at 128 rows: 800 tiles, 32 in the fourth
-  // round of 256 workgroups). Which rows a tile shape covers depends only on L and TNV, so an
-  // instance's arithmetic is the same alone and in any batch.
-  constexpr int TNS = TNV >= 128 ? TNV / 2 : TNV;
+  // tiles of TNS rows. The walks take row tiles in increasing order, so these come in the last round
+  // of workgroups, which otherwise costs a whole round of TNV-row tiles however few of them it holds
+  // (4096 instances x 3200 rows at 128 rows: 800 tiles, 32 in the fourth round of 256 workgroups; an
+  // iteration takes 312 us with 128 tiles of 32 rows in that round, 339 with 64 of 64 rows, BF16x3). An
+  // element's products and their order are the same in every shape, so an instance's arithmetic is
+  // the same alone and in any batch.
+  constexpr int TNS = small_rows<TNV>();
   const int nbig = TNV >= 128 ? (L - 1) / TNV : (L + TNV - 1) / TNV;
   const int ntiles_n = nbig + (L - nbig * TNV + TNS - 1) / TNS;
   const float alpha = (float)a.alpha, oma = (float)(1.0 - a.alpha), sigma = (float)a.sigma;
@@ -1079,7 +1086,7 @@ __global__ void __launch_bounds__(BS) batch_kernel(BatchArgs a_in) {
 
 template <int TNV>
 constexpr size_t kernel_smem() {
-  constexpr int small = TNV > 64 ? TNV / 2 : 32;  // the smaller row tiles of the same kernel
+  constexpr int small = TNV == 64 ? 32 : small_rows<TNV>();  // the smaller row tiles of the same kernel
   constexpr size_t layer = LayerGeo<TNV>::SMEM > LayerGeo<small>::SMEM ? LayerGeo<TNV>::SMEM : LayerGeo<small>::SMEM;
   return layer > CheckGeo::SMEM ? layer : CheckGeo::SMEM;
 }

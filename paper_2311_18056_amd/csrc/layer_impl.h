@@ -46,7 +46,18 @@ constexpr unsigned kSpinLimit = 1u << 22;
 // rows, 2.68 at 2400, 1.76 at 800, and 5.96 us at 3000 FP64 rows; with the pause 1.83, 1.69, 1.37 and
 // 3.17. Half the pause and one and a half times it cost about 15 % and 10 %; a pause that adapts to
 // whether the first poll hits settles longer or shorter than the best and was 5-20 % slower.
-constexpr int kPollWait = 18;
+// The best pause grows with the words and the workgroups: 1.58 us at a pause of 12 and 1.67 at 18 for 156
+// FP64 rows on 13 workgroups, 3.17 at 18 and 3.04 at 24 for 3000 FP64 rows on 240.
+constexpr int kPollWait = 18, kPollWaitFew = 12, kPollWaitMany = 24;
+template <typename T>
+__device__ __forceinline__ void poll_wait(int L) {
+  if (gridDim.x < 32)
+    __builtin_amdgcn_s_sleep(kPollWaitFew);
+  else if (sizeof(T) == sizeof(double) && gridDim.x * L > 256 * 1024)
+    __builtin_amdgcn_s_sleep(kPollWaitMany);
+  else
+    __builtin_amdgcn_s_sleep(kPollWait);
+}
 constexpr int kPollSleep = 1;
 
 template <typename T>
@@ -85,7 +96,7 @@ __device__ __forceinline__ bool gather(const uint64_t* buf, int L, int cs, bool 
                                        const unsigned* err, uint32_t etag) {
   bool ok = true;
   unsigned spins = 0;
-  __builtin_amdgcn_s_sleep(kPollWait);
+  poll_wait<T>(L);
   if constexpr (sizeof(T) == sizeof(float)) {
     uint64_t w[NC];
     const uint64_t* const p = buf + threadIdx.x;
@@ -716,7 +727,7 @@ __global__ void __launch_bounds__(BS) layer_kernel(LayerArgs a_in) {
   const int nrows = rbase + (g < rextra ? 1 : 0);
   const int r0 = g * rbase + (g < rextra ? g : rextra);
   const int nlds = nrows - NRS < a.lds_rows ? nrows - NRS : a.lds_rows;  // rows in LDS (none if <= 0)
-  constexpr int RP = sizeof(T) == sizeof(float) ? 16 : 8;                 // register rows reduced together
+  constexpr int RP = NRS > 8 && NC * words<T>() <= 5 ? 16 : 8;             // register rows reduced together
   constexpr int EB = NC * words<T>() <= 4 ? 8 : (NC * words<T>() <= 8 ? 4 : 2);  // further rows at a time
   const int cs = a.col_lanes;                                     // columns are spread over lanes 0 .. cs - 1
   const bool wave_on = wave * kWave < cs;                         // this wave holds columns

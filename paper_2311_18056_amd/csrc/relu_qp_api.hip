@@ -537,15 +537,20 @@ int set_grid(relu_qp_handle* h, int grid) {
 // more rows than a workgroup holds on chip (measured best at 2400 and 3200 rows in FP32).
 constexpr double kPlainRowsPerGroup = 12.5;
 
+// Closed loops spend their steps on exchanges and short row updates: 10.6 us per step of two FP64
+// iterations at 800 rows with 8 rows per workgroup, 10.9 with 12.5, 11.4 with one workgroup per compute
+// unit (240 rows: 8.1, 8.3, 8.7; 1360 rows: 12.3, 12.4, 12.4).
+constexpr int kLoopRowsPerGroup = 8;
+
 int choose_grid(relu_qp_handle* h) {
   int cus = 0, dev = 0;
   HIP_OR_FAIL(hipGetDevice(&dev));
   HIP_OR_FAIL(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
   const int need = (h->L + rqp::kMaxRows - 1) / rqp::kMaxRows;
-  int g = cus < h->L ? cus : h->L;
-  if (g > 256) g = 256;
+  // closed loops and scaled problems: a workgroup per kLoopRowsPerGroup rows, at most one per CU
+  int g = std::min(std::min(cus, 256), (h->L + kLoopRowsPerGroup - 1) / kLoopRowsPerGroup);
   if (g < need) g = need;
-  const int rc = set_grid(h, g);  // closed loops and scaled problems: one workgroup per CU
+  const int rc = set_grid(h, g);
   if (rc != RQP_OK) return rc;
   // plain solves: about kPlainRowsPerGroup rows per workgroup, at most the rows the kernel keeps
   // on chip (registers + LDS), and at most the grid above
