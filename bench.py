@@ -461,8 +461,8 @@ def bench_single(args, workload, x0_scale, steps, warmup, probes=True, latency_s
         "traffic_frac_of_peak": None if traffic_bytes is None else traffic_bytes / avg_launch_s / 1e9 / HBM_PEAK_GBS,
         "traffic_bytes_per_launch": traffic_bytes,
         "traffic_source": traffic_src,
-        "kernel": ("layer_kernel<float, 4, 8, 8, false>" if workload == "c1"
-                   else "small_kernel<double, 8, 8>" if small and grid_wg == 1
+        "kernel": ("layer_kernel<float, 4, 13, false>" if workload == "c1"
+                   else "small_kernel<double, 3>" if small and grid_wg == 1
                    else f"layer_kernel<{'double' if small else 'float'}, ...>"),
         "alg_bytes_per_unit": bytes_per_unit,
         "avg_launch_us": float(np.mean(kern_ms) * 1e3),

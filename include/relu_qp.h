@@ -255,8 +255,7 @@ int relu_qp_step(relu_qp_handle* h, int n_checks, void* stream, relu_qp_result* 
  * are idle and the state zero afterwards). The choice and timings are cached for the rest of the
  * process per device and problem shape (n, m, batch, precision, number of penalties): a later
  * handle of the same shape (a family loaded again) takes them without timing. The shapes
- * agree to rounding (the same products per element, issued to the matrix cores in another
- * interleaving).
+ * agree at least to rounding (each element takes the same products in every shape).
  * relu_qp_get_tile: the shape in use and, in us_per_iter[3] (may be NULL), the autotuner's
  * microseconds per iteration for 128, 64 and 256 rows. relu_qp_set_tile: force 128, 64 or 256,
  * or 0 for the autotuner's choice. RQP_ESTATE on a single-instance handle. */

@@ -6,7 +6,7 @@
 // with V[b] = [sigma x_b - q_b ; rho_b z_b - y_b], followed by the row-local update of the
 // single-instance kernel (relaxation, clamp, dual update) fused into the GEMM epilogue, which
 // also writes the next V. Instances are grouped by penalty index so that a tile of 128
-// instances uses one matrix; tiles are 128 instances x 128 layer rows, K in steps of 32.
+// instances uses one matrix; tiles are 128 instances x 256, 128, 64 or 32 layer rows, K in steps of 32.
 //
 // Precision: FP32 operands on v_mfma_f32_32x32x2_f32, or BF16 high/low splits of both operands
 // with three products hi*hi + lo*hi + hi*lo on v_mfma_f32_32x32x16_bf16 (FP32 accumulation),
@@ -61,8 +61,9 @@ enum { N_RP = 0, N_RD, N_AX, N_Z, N_PX, N_ATY, N_Q };
 // the workgroup have waited for their stores first) and one invalidates after the wait; the polls
 // are relaxed. With the fences in every wave, and an acquire (an L2 invalidate) per poll, the
 // barrier cost tens of microseconds and threw the operands of running tiles out of the L2s: an
-// iteration of 128 instances took 95 us at n = m = 200 (25 now) and 345 us at n = m = 1600 (59
-// now), one of 4096 instances at n = m = 1600 took 537 us (331 now; all BF16x3).
+// iteration of 128 instances took 95 us at n = m = 200 and 345 us at n = m = 1600, one of 4096
+// instances at n = m = 1600 took 537 us; with this barrier 25, 59 and 331 us (all BF16x3; 16, 44 and
+// 312 us with the tile shapes and reads that followed it).
 // Returns false if a wait exceeded the spin bound or another workgroup gave up (bar[1] set);
 // every workgroup then leaves the kernel.
 // acquire = false: the caller reads what other workgroups wrote with agent-scope reads only, so the L2

@@ -13,16 +13,17 @@
 // precomputes the products of D with A.
 //
 // Parallel layout: workgroup g owns a contiguous block of rows of Wc (row-parallel, Sec.
-// III-A). Lane t of a workgroup owns the columns c = t + 1024 k of every row of the block and
-// keeps the first NRS rows of its columns in registers for the whole launch (reloaded only
+// III-A). Lane t of the first col_lanes owns the columns c = t + col_lanes k of every row of the
+// block and keeps the first NRS rows of its columns in registers for the whole launch (reloaded only
 // when the penalty changes); further rows sit in LDS or stream from memory. After the row-local
 // update each row owner publishes its entry of the next w as an 8-byte {value, tag} word; every
 // lane polls the words of its own columns until the tags match. That single round trip is both
 // the data exchange and the synchronisation: there is no grid barrier.
 //
-// What bounds it: the exchange (1.83 us alone for 3200 words over 256 workgroups, 1.5 us for 1600
-// over 128; neither half the bytes per word nor wider polls shorten it, so it is latency), then the
-// multiply-adds and the reduction over lanes.
+// What bounds it: the exchange (alone, polled at once, 1.83 us for 3200 words over 256 workgroups and 1.5 us
+// for 1600 over 128; neither half the bytes per word nor wider polls shorten it, so it is latency), then the
+// multiply-adds and the reduction over lanes. A whole iteration took 3.4 us at 3200 FP32 rows with
+// the reduction row by row and no pause, and takes 1.77; a check took 21 us and takes 14.
 //
 // Every check_interval iterations (Sec. III-C) the owners publish [x; y], every workgroup
 // forms its rows of [P, A'; A, 0][x; y] with FP64 accumulation, reduces seven inf-norms as
@@ -43,8 +44,8 @@ constexpr unsigned kSpinLimit = 1u << 22;
 // Pauses (in units of 64 clocks) before the first poll of an exchange and between polls. A poll of all
 // words by all workgroups moves megabytes over the fabric, and one that comes before the words can be
 // there delays the words themselves: with the first poll at once an iteration took 2.96 us at 3200 FP32
-// rows, 2.68 at 2400, 1.76 at 800, and 5.96 us at 3000 FP64 rows; with the pause 1.83, 1.69, 1.37 and
-// 3.17. Half the pause and one and a half times it cost about 15 % and 10 %; a pause that adapts to
+// rows, 2.68 at 2400, 1.76 at 800, and 5.96 us at 3000 FP64 rows; with the pause 1.77, 1.65, 1.36 and
+// 3.03. Half the pause and one and a half times it cost about 15 % and 10 %; a pause that adapts to
 // whether the first poll hits settles longer or shorter than the best and was 5-20 % slower.
 // The best pause grows with the words and the workgroups: 1.58 us at a pause of 12 and 1.67 at 18 for 156
 // FP64 rows on 13 workgroups, 3.17 at 18 and 3.04 at 24 for 3000 FP64 rows on 240.

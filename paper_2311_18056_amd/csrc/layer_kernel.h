@@ -134,9 +134,10 @@ constexpr int layer_reg_rows(int nc) {
 // of its 13 rows over its lanes however few columns a lane has, so fewer, fuller waves run fewer
 // instructions; but every column is one more polled word per lane. In units of instructions of the
 // busiest SIMD: waves per SIMD times (13 per column plus the reduction's, about 64 in FP32 and 140 in
-// FP64), plus 90 per polled word, which puts the measured optima in order (us per iteration at 1024 /
-// 832 / 640 / 512 / 256 lanes: 3200 FP32 rows 2.97 / 2.98 / 3.09 / 3.83 / -, 2400 rows 2.71 / 2.67 / 2.77 /
-// 2.77 / -, 800 rows 1.81 / 1.80 / 1.76 / 1.72 / 1.74; 800 FP64 rows 2.44 / 2.43 / 2.29 / 2.14 / 2.83).
+// FP64), plus 90 per polled word: within 2 % of the best of the measured lane counts at each size (us per
+// iteration at the rule's / 1024 / 640 / 512 / 256 lanes: 3200 FP32 rows 1.77 / 1.73 / 1.84 / - / -, 2400 rows
+// 1.65 / 1.68 / 1.63 / 1.65 / -, 800 rows 1.36 / 1.49 / 1.41 / 1.37 / 1.45; 800 FP64 rows 1.76 / 1.99 / 1.92 /
+// 1.76 / -, 156 rows 1.55 / 1.91 / 1.72 / 1.59 / 1.52; -: too few lanes for these columns).
 template <typename T>
 inline int layer_col_lanes(int L) {
   const int most = sizeof(T) == sizeof(double) ? 2 : 5, red = sizeof(T) == sizeof(double) ? 140 : 64;

@@ -782,11 +782,10 @@ int launch_batched(relu_qp_handle* h, int steps, hipStream_t st, relu_qp_result*
   return RQP_OK;
 }
 
-// Autotuner of the batched GEMM's tile shape (128 or 64 matrix rows per tile): each shape runs
+// Autotuner of the batched GEMM's tile shape (128, 64 or 256 matrix rows per tile): each shape runs
 // two check intervals of every slot from a cold start on the handle's own data, timed with HIP
-// events; the faster one is kept. Slots, statuses and state are reset to idle afterwards. The
-// shapes agree to rounding (every accumulator element sees the same products, in another
-// interleaving on the matrix cores): few tiles (small batches) favour 64 rows, many 128.
+// events; the fastest is kept. Slots, statuses and state are reset to idle afterwards. Few tiles
+// (small batches) favour 64 rows, many the larger shapes.
 // The choice is cached per process and device for the problem shape (n, m, batch, precision,
 // penalties): a family loaded again (or another handle of the same shape) takes the cached
 // choice and timings without timing again.
