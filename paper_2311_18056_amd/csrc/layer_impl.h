@@ -122,8 +122,11 @@ __device__ __forceinline__ bool gather(const uint64_t* buf, int L, int cs, bool 
     u32x4 w[NC];
     while (true) {
 #pragma unroll
-      for (int k = 0; k < NC; ++k)  // past L: reads zero
+      for (int k = 0; k < NC - 1; ++k)
         w[k] = __builtin_amdgcn_raw_buffer_load_b128(rs, threadIdx.x * 16u, k * cs * 16, kAgentScope);
+      // the column that can lie past L (reads zero) by the lane's offset alone: the uniform offset is no
+      // part of the bounds check's contract
+      w[NC - 1] = __builtin_amdgcn_raw_buffer_load_b128(rs, (threadIdx.x + cs * (NC - 1)) * 16u, 0, kAgentScope);
       bool all = true;
 #pragma unroll
       for (int k = 0; k < NC; ++k) all &= (w[k].y == tag && w[k].w == tag) || (k == NC - 1 && !last);
@@ -154,7 +157,7 @@ __device__ __forceinline__ bool gather_norms(const uint64_t* buf, int count, uin
   __builtin_amdgcn_s_sleep(kPollWait);
   while (true) {
     w0 = __builtin_amdgcn_raw_buffer_load_b128(rs, tid * 16u, 0, kAgentScope);
-    w1 = __builtin_amdgcn_raw_buffer_load_b128(rs, tid * 16u, BS * 16, kAgentScope);
+    w1 = __builtin_amdgcn_raw_buffer_load_b128(rs, (tid + BS) * 16u, 0, kAgentScope);
     const bool miss = (in0 && (w0.y != tag || w0.w != tag)) || (in1 && (w1.y != tag || w1.w != tag));
     asm volatile("" ::: "memory");
     if (__builtin_amdgcn_ballot_w64(miss) == 0) break;
