@@ -748,7 +748,7 @@ __global__ void __launch_bounds__(BS) layer_kernel(LayerArgs a_in) {
   // Solves s = 0 .. count-1 run one after another in this launch; the weights of the active
   // penalty stay on chip between them. Solve s uses tags tag0 + s * span, takes its data from
   // x0 + s * nx (when given) and writes its results at index s of the outputs.
-  const uint32_t span = (uint32_t)a.max_iter + 2u;
+  const uint32_t span = solve_span(a.max_iter);
   const int ci = a.check_interval, max_iter = a.max_iter;
   __shared__ RowState<T> rs;
   const bool own = tid < nrows, xrow = r0 + tid < n;
@@ -964,7 +964,7 @@ __global__ void __launch_bounds__(BS) layer_kernel(LayerArgs a_in) {
           w = rho * s - y;
           pre = fma(oma, s, y / rho);
         }
-        ll_store(a.xw + ((long)((k0 + 1) & 1) * L + R) * NW, w, tag + (uint32_t)(k0 + 1));
+        ll_store(a.xw + ((long)word_half(tag, k0 + 1) * L + R) * NW, w, tag + (uint32_t)(k0 + 1));
         rs.pre[tid] = pre;
       }
     };
@@ -989,7 +989,7 @@ __global__ void __launch_bounds__(BS) layer_kernel(LayerArgs a_in) {
           T(*const rk)[NWAVE] = red[k & 1];
           if (wave_on) {
             T wv[NC];
-            if (!gather<T, NC>(xw + (long)(k & 1) * L * NW, L, cs, last, tag + (uint32_t)k, wv, a.err, tag))
+            if (!gather<T, NC>(xw + (long)word_half(tag, k) * L * NW, L, cs, last, tag + (uint32_t)k, wv, a.err, tag))
               fail_flag = 1;
             // register rows, RP at a time: products, then one multi-row wave reduction
 #pragma unroll
@@ -1053,7 +1053,7 @@ __global__ void __launch_bounds__(BS) layer_kernel(LayerArgs a_in) {
           if (own) {
             const T pre = rs.pre[tid], q = rs.q[tid];
             const T v = sum_waves(rk[tid]);
-            uint64_t* const xo = xw + ((long)((k + 1) & 1) * L + R) * NW;
+            uint64_t* const xo = xw + ((long)word_half(tag, k + 1) * L + R) * NW;
             const T t = fma(alpha, v, pre);
             if (xrow) {
               if (k < kend) ll_store(xo, sigma * t - q, tag + (uint32_t)(k + 1));

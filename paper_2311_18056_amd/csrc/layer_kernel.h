@@ -90,6 +90,17 @@ constexpr int kLayerBlock = 1024;
 constexpr int kMaxLayerRows = 8 * kLayerBlock;
 constexpr int kMaxRows = 64;
 
+// The two halves of the layer-input words. Word k (k = 1, 2, ...) of a solve whose tags start at `tag`
+// carries tag + k and lies in half word_half(tag, k). Two consecutive words of a launch must lie in
+// different halves: a workgroup overwrites word i by word i + 2 only after it gathered all of word i + 1,
+// which every workgroup publishes only after it gathered all of word i, so nobody still polls for the word
+// that is lost. Consecutive over the end of a solve too: a closed loop's step can end without a check, and
+// the next one's first word is then held back by the owners of the applied control alone. With the half
+// taken from the tag, word k = max_iter is followed by tag + solve_span(max_iter) + 1 = (tag + k) + 3. (A
+// step that ends earlier ends at a check, whose exchanges wait for every workgroup.)
+__host__ __device__ inline uint32_t solve_span(int max_iter) { return (uint32_t)max_iter + 2u; }  // tags of a solve
+__host__ __device__ inline int word_half(uint32_t tag, int k) { return (int)((tag + (uint32_t)k) & 1u); }
+
 // Split of the residual check over the workgroups. The check reads n L entries of [P, A'] for
 // the x rows (dual side) and n m of [A, 0] for the constraint rows (primal side); each
 // workgroup forms the constraint rows it owns in the layer (rows split evenly, L / G each), and

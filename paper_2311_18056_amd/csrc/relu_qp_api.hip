@@ -1404,7 +1404,7 @@ int check_single_call(relu_qp_handle* h, const double* x0, int count, relu_qp_re
   if (x0 && !h->F_d) return fail(RQP_ESTATE, "relu_qp_set_parametric has not been called");
   if (count < 1) return fail(RQP_EINVAL, "count must be >= 1");
   if (count > 1 && h->batched) return fail(RQP_EINVAL, "solve sequences run on the single-instance engine");
-  const uint64_t span = (uint64_t)h->s.max_iter + 2u;
+  const uint64_t span = rqp::solve_span(h->s.max_iter);
   if (span * (uint64_t)count >= 0x7fffffffull) return fail(RQP_EINVAL, "count * (max_iter + 2) must stay below 2^31");
   return RQP_OK;
 }
@@ -1420,7 +1420,7 @@ int solve_impl(relu_qp_handle* h, const double* x0, int count, void* stream, rel
                                                 static_cast<float*>(h->u), st));
     return solve_batched(h, st, out);
   }
-  const uint32_t span = (uint32_t)h->s.max_iter + 2u;
+  const uint32_t span = rqp::solve_span(h->s.max_iter);
   if ((uint64_t)h->tag + (uint64_t)span * count >= 0xffffffffull) {
     // restart the tag sequence: clear every exchange word so no stale tag can match
     HIP_OR_FAIL(hipMemsetAsync(h->xw, 0, h->xw_words * 8, st));
@@ -1475,7 +1475,7 @@ int relu_qp_solve_x0_noalloc(relu_qp_handle* h, const double* x0, void* stream, 
     std::lock_guard<std::mutex> lock(g_scratch_mu);
     ScratchDev& sd = g_scratch[h->device];
     if (!sd.ptr) return fail(RQP_ESTATE, "no scratch on device %d", h->device);
-    const uint32_t span = (uint32_t)h->s.max_iter + 2u;
+    const uint32_t span = rqp::solve_span(h->s.max_iter);
     unsigned char* base = static_cast<unsigned char*>(sd.ptr);
     if (!sd.clean || (uint64_t)sd.tag + span >= 0xffffffffull) {
       // first use on this GPU, or the tag sequence restarts: no stale tag may match
