@@ -313,8 +313,8 @@ __device__ __forceinline__ void cache_slice(const LayerArgs& a, const CheckRows<
 // its lanes once per row it touches instead of every wave once per row. body[i]: the sums of the
 // wave that holds row i's first unit; head[w]: those of wave w for row head_row[w], which it starts in
 // the middle of (-1: none). Each entry: the product with the x part (P x, or A x), with the y part
-// (A'y), both FP64 sums of the exact FP64 products, and (FP32 only) the sum of the absolute values of
-// the products, accumulated in FP32 (it only enters the rounding bound).
+// (A'y), and (FP32 only: the rounding bound) the sum of the absolute values of the products, all FP64
+// sums of the exact FP64 products.
 constexpr int kUnit = 4 * kWave;
 struct CheckSums {
   double body[kMaxCheckRows + kMaxRows][3];
@@ -362,8 +362,7 @@ __device__ __forceinline__ void check_products(const LayerArgs& a, const CheckRo
   int un = t0 < nd ? t0 % ud : (t0 - nd) % up;
   if (lane == 0) cs.head_row[wave] = un != 0 ? row : -1;
   double* dst = un != 0 ? cs.head[wave] : cs.body[row];
-  double p = 0.0, q = 0.0;
-  float fa = 0.0f;
+  double p = 0.0, q = 0.0, f = 0.0;
   // this lane's four entries of unit u of row r
   auto load = [&](int r, int u, T(&w)[4]) __attribute__((always_inline)) {
     const bool dual = r < cr.nck;
@@ -408,17 +407,21 @@ __device__ __forceinline__ void check_products(const LayerArgs& a, const CheckRo
     }
     if constexpr (F32) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) fa = fmaf(fabsf(w[e]), fabsf(v[e]), fa);
+      for (int e = 0; e < 4; ++e) f = fma(fabs((double)w[e]), fabs((double)v[e]), f);
     }
     if (end || t + 1 == t1) {
-      double pq[2] = {p, q};
-      const double s = reduce_rows<2>(pq);  // lanes 0 and 32 hold p and q
-      if (row_writer<2>()) dst[lane >> 5] = s;
-      if constexpr (F32) fa = wave_sum_to_last(fa);
-      if (lane == kLastLane) dst[2] = (double)fa;
+      if constexpr (F32) {
+        double pqf[4] = {p, q, f, 0.0};
+        const double s = reduce_rows<4>(pqf);  // lanes 0, 16 and 32 hold p, q and f
+        if (row_writer<4>() && lane < 48) dst[lane >> 4] = s;
+      } else {
+        double pq[2] = {p, q};
+        const double s = reduce_rows<2>(pq);  // lanes 0 and 32 hold p and q
+        if (row_writer<2>()) dst[lane >> 5] = s;
+      }
       p = 0.0;
       q = 0.0;
-      fa = 0.0f;
+      f = 0.0;
       dst = cs.body[row2];
     }
     row = row2;
@@ -431,9 +434,9 @@ __device__ __forceinline__ void check_products(const LayerArgs& a, const CheckRo
 // Bound factor of the check in FP32: with the stored matrices and the returned x, z, y rounded
 // to FP32 (unit roundoff u = 2^-24), the products exact in FP64 and FP64 accumulation over at
 // most L terms here and in the CPU's evaluation, |computed - FP64 value| <= kappa0 * sum |a v|
-// per row with kappa0 = 2u + 2 (L + 8) 2^-53; the sum of absolute values is itself accumulated
-// in FP32 (relative error below 1e-3 for L <= 8192), hence the factor 1.02. FP64 handles
-// compute the FP64 residual itself (0).
+// per row with kappa0 = 2u + 2 (L + 8) 2^-53. The sum of absolute values is an FP64 sum like the others,
+// so the factor 1.02 is room to spare (the rounding of the bound and of its own sum is below 1e-12).
+// FP64 handles compute the FP64 residual itself (0).
 template <typename T>
 __device__ __forceinline__ double check_kappa(int L) {
   if constexpr (sizeof(T) == sizeof(double)) {
