@@ -406,8 +406,10 @@ __device__ __forceinline__ void check_products(const LayerArgs& a, const CheckRo
       }
     }
     if constexpr (F32) {
+      double t = fabs((double)w[0]) * fabs((double)v[0]);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) f = fma(fabs((double)w[e]), fabs((double)v[e]), f);
+      for (int e = 1; e < 4; ++e) t = fma(fabs((double)w[e]), fabs((double)v[e]), t);
+      f += t;
     }
     if (end || t + 1 == t1) {
       if constexpr (F32) {
