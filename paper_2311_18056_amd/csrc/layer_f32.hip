@@ -2,5 +2,5 @@
 #include "layer_impl.h"
 
 namespace rqp {
-const void* layer_fn_f32(int nc) { return fn_for<float, false>(nc); }
+const void* layer_fn_f32(int nc, bool more) { return fn_for<float, false>(nc, more); }
 }  // namespace rqp

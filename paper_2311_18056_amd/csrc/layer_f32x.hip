@@ -2,5 +2,5 @@
 #include "layer_impl.h"
 
 namespace rqp {
-const void* layer_fn_f32x(int nc) { return fn_for<float, true>(nc); }
+const void* layer_fn_f32x(int nc, bool more) { return fn_for<float, true>(nc, more); }
 }  // namespace rqp

@@ -2,5 +2,5 @@
 #include "layer_impl.h"
 
 namespace rqp {
-const void* layer_fn_f64(int nc) { return fn_for<double, false>(nc); }
+const void* layer_fn_f64(int nc, bool more) { return fn_for<double, false>(nc, more); }
 }  // namespace rqp

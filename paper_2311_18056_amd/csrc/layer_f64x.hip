@@ -2,5 +2,5 @@
 #include "layer_impl.h"
 
 namespace rqp {
-const void* layer_fn_f64x(int nc) { return fn_for<double, true>(nc); }
+const void* layer_fn_f64x(int nc, bool more) { return fn_for<double, true>(nc, more); }
 }  // namespace rqp

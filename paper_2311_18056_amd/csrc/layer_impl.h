@@ -737,7 +737,7 @@ __global__ void __launch_bounds__(BS) layer_kernel(LayerArgs a_in) {
   const int r0 = g * rbase + (g < rextra ? g : rextra);
   const int nlds = nrows - NRS < a.lds_rows ? nrows - NRS : a.lds_rows;  // rows in LDS (none if <= 0)
   constexpr int RP = NRS > 8 && NC * words<T>() <= 5 ? 16 : 8;             // register rows reduced together
-  constexpr int EB = NC * words<T>() <= 4 ? 8 : (NC * words<T>() <= 8 ? 4 : 2);  // further rows at a time
+  constexpr int EB = layer_pass_rows<T>(NC);                               // further rows at a time
   const int cs = a.col_lanes;                                     // columns are spread over lanes 0 .. cs - 1
   const bool wave_on = wave * kWave < cs;                         // this wave holds columns
   const bool last = tid < cs && tid + cs * (NC - 1) < L;          // this lane's last column exists
@@ -1131,17 +1131,24 @@ __global__ void __launch_bounds__(BS) layer_kernel(LayerArgs a_in) {
   }
 }
 
+// The kernel for nc columns per lane, with layer_reg_rows or (more) layer_more_rows rows in registers.
+template <typename T, int NC, bool XT>
+const void* fn_at(bool more) {
+  constexpr int A = layer_reg_rows<T>(NC), B = layer_more_rows<T>(NC);
+  return more ? reinterpret_cast<const void*>(&layer_kernel<T, NC, B, XT>)
+              : reinterpret_cast<const void*>(&layer_kernel<T, NC, A, XT>);
+}
 template <typename T, bool XT>
-const void* fn_for(int nc) {
+const void* fn_for(int nc, bool more) {
   switch (nc) {
-    case 1: return reinterpret_cast<const void*>(&layer_kernel<T, 1, layer_reg_rows<T>(1), XT>);
-    case 2: return reinterpret_cast<const void*>(&layer_kernel<T, 2, layer_reg_rows<T>(2), XT>);
-    case 3: return reinterpret_cast<const void*>(&layer_kernel<T, 3, layer_reg_rows<T>(3), XT>);
-    case 4: return reinterpret_cast<const void*>(&layer_kernel<T, 4, layer_reg_rows<T>(4), XT>);
-    case 5: return reinterpret_cast<const void*>(&layer_kernel<T, 5, layer_reg_rows<T>(5), XT>);
-    case 6: return reinterpret_cast<const void*>(&layer_kernel<T, 6, layer_reg_rows<T>(6), XT>);
-    case 7: return reinterpret_cast<const void*>(&layer_kernel<T, 7, layer_reg_rows<T>(7), XT>);
-    case 8: return reinterpret_cast<const void*>(&layer_kernel<T, 8, layer_reg_rows<T>(8), XT>);
+    case 1: return fn_at<T, 1, XT>(more);
+    case 2: return fn_at<T, 2, XT>(more);
+    case 3: return fn_at<T, 3, XT>(more);
+    case 4: return fn_at<T, 4, XT>(more);
+    case 5: return fn_at<T, 5, XT>(more);
+    case 6: return fn_at<T, 6, XT>(more);
+    case 7: return fn_at<T, 7, XT>(more);
+    case 8: return fn_at<T, 8, XT>(more);
     default: return nullptr;
   }
 }

@@ -140,6 +140,28 @@ template <typename T>
 constexpr int layer_reg_rows(int nc) {
   return sizeof(T) == sizeof(double) ? (nc <= 2 ? 13 : 32 / nc) : (nc <= 5 ? 13 : 64 / nc);
 }
+// Further rows are multiplied this many at a time, each pass with a read of LDS (or memory) and a reduction
+// over the lanes of its own.
+template <typename T>
+constexpr int layer_pass_rows(int nc) {
+  const int regs = nc * (int)sizeof(T) / 4;
+  return regs <= 4 ? 8 : (regs <= 8 ? 4 : 2);
+}
+// An instantiation for blocks of more rows (a smaller grid, or more than 3328 rows in all) keeps as many in
+// registers as fit the same 64, at most 32, in whole groups of the 16 that are reduced together. It is
+// taken where it saves a pass: 200 iterations of 1600 FP32 rows at 20 / 24 / 32 rows a block took 524 / 687 /
+// 842 us with 13 rows in registers and take 453 / 452 / 454 with 32; at 3200 rows and 24 a block 876 and 673
+// with 16, but at 20 a block, one pass either way, 615 and 672: its rows cost registers and products too.
+template <typename T>
+constexpr int layer_more_rows(int nc) {
+  const int most = (sizeof(T) == sizeof(double) ? 32 : 64) / nc / 16 * 16;
+  return most > 32 ? 32 : (most > layer_reg_rows<T>(nc) ? most : layer_reg_rows<T>(nc));
+}
+template <typename T>
+constexpr bool layer_takes_more(int nc, int rows) {
+  const int pass = layer_pass_rows<T>(nc), a = rows - layer_reg_rows<T>(nc), b = rows - layer_more_rows<T>(nc);
+  return (b > 0 ? (b + pass - 1) / pass : 0) < (a > 0 ? (a + pass - 1) / pass : 0);
+}
 
 // Lanes (a multiple of the wave size) that hold the columns of the rows. A wave pays for the reduction
 // of its 13 rows over its lanes however few columns a lane has, so fewer, fuller waves run fewer
@@ -166,8 +188,8 @@ inline int layer_col_lanes(int L) {
 }
 
 // Kernel choice and resources for a problem on `grid` workgroups: the first layer_reg_rows rows of
-// each block stay in registers and the next lds_rows in LDS for the whole launch; further rows
-// stream from memory every iteration.
+// each block (layer_more_rows where that saves a pass) stay in registers and the next lds_rows in LDS for the
+// whole launch; further rows stream from memory every iteration.
 struct LaunchPlan {
   const void* fn;
   int lds_rows;

@@ -7,10 +7,10 @@
 
 namespace rqp {
 
-const void* layer_fn_f32(int nc);
-const void* layer_fn_f32x(int nc);
-const void* layer_fn_f64(int nc);
-const void* layer_fn_f64x(int nc);
+const void* layer_fn_f32(int nc, bool more);
+const void* layer_fn_f32x(int nc, bool more);
+const void* layer_fn_f64(int nc, bool more);
+const void* layer_fn_f64x(int nc, bool more);
 
 template <typename T>
 LaunchPlan plan_layer(int n, int m, int grid, bool xt) {
@@ -18,8 +18,11 @@ LaunchPlan plan_layer(int n, int m, int grid, bool xt) {
   const int L = n + m;
   if (L < 1 || L > kMaxLayerRows || grid < 1) return p;
   const int cs = layer_col_lanes<T>(L), nc = (L + cs - 1) / cs;
-  const void* fn = sizeof(T) == sizeof(double) ? (xt ? layer_fn_f64x(nc) : layer_fn_f64(nc))
-                                               : (xt ? layer_fn_f32x(nc) : layer_fn_f32(nc));
+  const int rows = (L + grid - 1) / grid;
+  const bool more = layer_takes_more<T>(nc, rows);
+  const int reg = more ? layer_more_rows<T>(nc) : layer_reg_rows<T>(nc);
+  const void* fn = sizeof(T) == sizeof(double) ? (xt ? layer_fn_f64x(nc, more) : layer_fn_f64(nc, more))
+                                               : (xt ? layer_fn_f32x(nc, more) : layer_fn_f32(nc, more));
   int dev = 0, smem_max = 0, cus = 0;
   if (hipGetDevice(&dev) != hipSuccess) return p;
   if (hipDeviceGetAttribute(&smem_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess) return p;
@@ -32,7 +35,6 @@ LaunchPlan plan_layer(int n, int m, int grid, bool xt) {
   const long stage = (L + 255) / 256 * 256;
   const long room = ((long)smem_max - (long)fa.sharedSizeBytes) / 16 * 16 - stage * es;
   if (room < 0) return p;
-  const int rows = (L + grid - 1) / grid, reg = layer_reg_rows<T>(nc);
   p.lds_rows = (int)std::min<long>(std::max(rows - reg, 0), room / row_bytes);
   p.on_chip = reg + (int)(room / row_bytes);
   // the check rows a workgroup has at most, in whole kilobytes (the copy's unit)
