@@ -44,9 +44,7 @@ __device__ __forceinline__ void static_for(F&& f) {
 }
 
 constexpr int BS = kBatchBlock;
-constexpr int TM = kTileM, TN = kTileN, TK = kTileK;
-constexpr int PADB = 8;  // bf16 row padding in LDS (elements)
-constexpr int PADF = 4;  // fp32 row padding in LDS (elements)
+constexpr int TM = kTileM, TK = kTileK;
 constexpr int kEarlyBlocks = 2;  // accumulator blocks per wave whose state is loaded before the products
 constexpr unsigned kBarSpin = 1u << 24;
 
@@ -157,7 +155,6 @@ __device__ __forceinline__ const T& at32(const T* base, unsigned idx) {
 // lane, the same chunk in all rows) then fall on distinct banks for every group of 8 or 16
 // lanes. Loads never branch: rows past a tile's valid range read valid padding rows (their
 // products land in results that are discarded).
-typedef __attribute__((address_space(3))) void* lds_ptr_t;
 template <int CPR>  // 16-byte chunks per row: 4 (BF16), 8 (FP32), 16 (FP64)
 __device__ __forceinline__ int swz(int r) {
   if constexpr (CPR == 4)
@@ -169,8 +166,7 @@ __device__ __forceinline__ int swz(int r) {
 }
 // ROWS rows of one K block starting at byte address src (rows CPR * 16 bytes apart) to lds; with PANEL,
 // several panels of PANEL rows each, src being the caller's wave's panel.
-// AUX: cache policy of the reads (kAgentScope: past this XCD's L2, which may hold older data).
-constexpr int kAgentScope = 16;
+// AUX: cache policy of the reads.
 template <int ROWS, int CPR, int PANEL = ROWS, int AUX = 0>
 __device__ __forceinline__ void dma_panel(const unsigned char* src, unsigned char* lds, int wave) {
   static_assert(ROWS * CPR % BS == 0, "a panel is a whole number of wave instructions per thread");
@@ -215,10 +211,11 @@ __device__ __forceinline__ void lds_barrier() {
 // one is multiplied; one barrier per stage (stage s has landed for every wave, and every wave is
 // done with the buffer that stage s + NST - 1 overwrites). issue(s, buf) starts the copy of
 // stage s (LOADS instructions per thread); comp(s, buf) multiplies it. On entry the LDS buffers
-// may still be read by the previous tile. Stores of the previous tile may still be in flight:
-// the vector memory counter also counts them, but they were issued before every copy of this
-// loop and copies complete in issue order, so "at most LOADS * k outstanding" still means that
-// every copy but the last k stages' has landed. Loads of the caller must be complete on entry.
+// may still be read by the previous tile. Stores of the previous tile and loads of the caller (a
+// tile's state, layer_step) may still be in flight: the vector memory counter also counts them, but
+// they were issued before every copy of this loop and copies complete in issue order, so "at most
+// LOADS * k outstanding" still means that every copy but the last k stages' has landed; whatever else
+// is outstanding only makes a wait longer. The caller issues no vector memory operation between copies.
 template <int NST, int LOADS, typename Issue, typename Comp>
 __device__ __forceinline__ void kloop(int s0, int s1, unsigned char* lds, int stage_bytes, Issue&& issue, Comp&& comp) {
   static_assert(NST >= 2 && LOADS * (NST - 2) < 64, "pipeline depth");
@@ -430,10 +427,11 @@ __device__ __forceinline__ void check_tile(unsigned char* lds, const double* A, 
 __device__ __forceinline__ int acc64_row(int wm, int i, int v, int lane) { return wm * 64 + i * 16 + lane / 16 + 4 * v; }
 __device__ __forceinline__ int acc64_col(int wn, int j, int lane) { return wn * 64 + j * 16 + lane % 16; }
 
-// Rows of the tiles that take the last TNV rows of the layer.
+// Rows of the smaller tiles of a kernel: those of the last TNV rows of the layer, or (64-row kernel)
+// those that the whole layer goes in where there are few.
 template <int TNV>
 constexpr int small_rows() {
-  return TNV >= 256 ? 128 : TNV >= 128 ? 32 : 64;
+  return TNV >= 256 ? 128 : 32;
 }
 
 // M-tile descriptor: {penalty index, offset into lists, instance count}
@@ -638,7 +636,7 @@ __global__ void __launch_bounds__(BS) batch_kernel(BatchArgs a_in) {
   // the same alone and in any batch.
   constexpr int TNS = small_rows<TNV>();
   const int nbig = TNV >= 128 ? (L - 1) / TNV : (L + TNV - 1) / TNV;
-  const int ntiles_n = nbig + (L - nbig * TNV + TNS - 1) / TNS;
+  const int ntiles_n = nbig + (TNV >= 128 ? (L - nbig * TNV + TNS - 1) / TNS : 0);
   const float alpha = (float)a.alpha, oma = (float)(1.0 - a.alpha), sigma = (float)a.sigma;
   const float eqs = (float)a.rho_eq_scale;
   unsigned epoch = 0;
@@ -890,12 +888,11 @@ __global__ void __launch_bounds__(BS) batch_kernel(BatchArgs a_in) {
         if (tid < TM) s_list[tid] = a.lists[d.off + (tid < d.cnt ? tid : 0)];
         __syncthreads();
       }
-      if (TNV == 64 && fine)
-        layer_step(std::integral_constant<int, 32>{}, *mt, list, nt * 32);
-      else if (nt < nbig)
+      const bool small = TNV == 64 ? fine : nt >= nbig;
+      if (!small)
         layer_step(std::integral_constant<int, TNV>{}, *mt, list, nt * TNV);
       else
-        layer_step(std::integral_constant<int, TNS>{}, *mt, list, nbig * TNV + (nt - nbig) * TNS);
+        layer_step(std::integral_constant<int, TNS>{}, *mt, list, TNV == 64 ? nt * TNS : nbig * TNV + (nt - nbig) * TNS);
     }
     // 32-row tiles read V at agent scope, and everything else an iteration reads is constant in the segment
     // or written by this workgroup
@@ -1087,7 +1084,7 @@ __global__ void __launch_bounds__(BS) batch_kernel(BatchArgs a_in) {
 
 template <int TNV>
 constexpr size_t kernel_smem() {
-  constexpr int small = TNV == 64 ? 32 : small_rows<TNV>();  // the smaller row tiles of the same kernel
+  constexpr int small = small_rows<TNV>();
   constexpr size_t layer = LayerGeo<TNV>::SMEM > LayerGeo<small>::SMEM ? LayerGeo<TNV>::SMEM : LayerGeo<small>::SMEM;
   return layer > CheckGeo::SMEM ? layer : CheckGeo::SMEM;
 }

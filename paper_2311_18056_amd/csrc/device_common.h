@@ -7,6 +7,14 @@ namespace rqp {
 
 constexpr int kWave = 64;
 
+// Cache policy of a load (sc1): past this XCD's L2, which may hold older data.
+constexpr int kAgentScope = 16;
+// 16 bytes per lane straight from memory to consecutive LDS bytes from lds (uniform).
+typedef __attribute__((address_space(3))) void* lds_ptr_t;
+__device__ __forceinline__ void lds_copy16(const void* src, void* lds) {
+  __builtin_amdgcn_global_load_lds(src, (lds_ptr_t)lds, 16, 0, 0);
+}
+
 // ---------------------------------------------------------------------------------------------
 // Flag-in-data exchange words. A producer publishes a value together with a 32-bit tag in one
 // 8-byte store; a consumer polls the 8-byte word until the tag matches. An aligned 8-byte
@@ -226,21 +234,6 @@ __device__ __forceinline__ int rows_held() {
 template <int R>
 __device__ __forceinline__ bool row_writer() {
   return ((threadIdx.x % kWave) & (kWave / R - 1)) == 0;
-}
-
-template <typename T>
-__device__ __forceinline__ T wave_sum(T v) {
-#pragma unroll
-  for (int off = kWave / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, kWave);
-  return v;
-}
-__device__ __forceinline__ uint64_t wave_max_u64(uint64_t v) {
-#pragma unroll
-  for (int off = kWave / 2; off > 0; off >>= 1) {
-    uint64_t o = __shfl_xor(v, off, kWave);
-    v = o > v ? o : v;
-  }
-  return v;
 }
 
 // Projection onto [l, u] (eq. clamp). Equal to t - ReLU(t - u) + ReLU(l - t) for l <= u, but

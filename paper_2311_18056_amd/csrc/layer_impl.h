@@ -47,8 +47,15 @@ constexpr unsigned kSpinLimit = 1u << 22;
 // rows, 2.68 at 2400, 1.76 at 800, and 5.96 us at 3000 FP64 rows; with the pause 1.77, 1.65, 1.36 and
 // 3.03. Half the pause and one and a half times it cost about 15 % and 10 %; a pause that adapts to
 // whether the first poll hits settles longer or shorter than the best and was 5-20 % slower.
-// The best pause grows with the words and the workgroups: 1.58 us at a pause of 12 and 1.67 at 18 for 156
-// FP64 rows on 13 workgroups, 3.17 at 18 and 3.04 at 24 for 3000 FP64 rows on 240.
+// The best pause grows with the words and the workgroups (us per iteration at pauses of 12 / 18 / 24; the
+// rule is within 2.7 % of the best of 8, 12, 18, 24 and 30 at 40 grids between 136 and 4000 rows):
+//   FP64, workgroups x rows: 11 x 136 1.46 / 1.51 / 1.67, 23 x 280 1.62 / 1.59 / 1.65, 32 x 400 1.69 / 1.60 /
+//     1.70, 88 x 1100 2.23 / 1.89 / 1.87, 128 x 1600 2.54 / 2.17 / 2.05, 160 x 2000 2.63 / 2.14 / 2.07,
+//     240 x 3000 3.93 / 3.17 / 2.99
+//   FP32: 16 x 200 1.28 / 1.33 / 1.49, 30 x 600 1.73 / 1.76 / 1.92, 32 x 400 1.35 / 1.31 / 1.45,
+//     128 x 1600 1.67 / 1.59 / 1.74, 240 x 3000 1.84 / 1.73 / 1.81
+// so below 32 workgroups 12 and 18 are level or 12 wins, from 32 on 18 does, and 24 where FP64 words reach
+// the quarter million. The norm partials' exchange is polled once a check and always waits kPollWait.
 constexpr int kPollWait = 18, kPollWaitFew = 12, kPollWaitMany = 24;
 template <typename T>
 __device__ __forceinline__ void poll_wait(int L) {
@@ -90,7 +97,6 @@ __device__ __forceinline__ void err_raise(unsigned* err, uint32_t tag) {
 // of the two words of a value together (FP64; each word is valid by its own tag). A lane leaves the loop
 // by itself: one exit for the whole wave, words awaited one after another, or two polls in flight all
 // took longer (1.67 us for an exchange of 3200 words over 256 workgroups; 1.85, 2.5 and 2.2 us).
-constexpr int kAgentScope = 16;  // cache policy of a buffer load: sc1
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 template <typename T, int NC>
 __device__ __forceinline__ bool gather(const uint64_t* buf, int L, int cs, bool last, uint32_t tag, T (&v)[NC],
@@ -277,16 +283,12 @@ __device__ __forceinline__ void load_quad(const double* p, double (&v)[4]) {
 template <typename T>
 struct CheckRows {
   int cb, nck, pb, np, cd, cp;
-  const T* cache;
+  T* cache;
 };
 
 // Slice s of the LDS copy: one 1 KB wave instruction per wave, straight from memory to LDS. The
 // slices are issued one per iteration of the first solve, behind the iteration's exchange, so that
 // the read of the check matrix costs the first check nothing.
-typedef __attribute__((address_space(3))) void* lds_ptr_t;
-__device__ __forceinline__ void lds_copy16(const unsigned char* src, const void* lds, int quad) {
-  __builtin_amdgcn_global_load_lds(src, (lds_ptr_t)((unsigned char*)lds + (size_t)quad * 16), 16, 0, 0);
-}
 template <typename T>
 __device__ __forceinline__ int cache_quads(const LayerArgs& a, const CheckRows<T>& cr) {
   constexpr int E = 16 / sizeof(T);
@@ -305,7 +307,7 @@ __device__ __forceinline__ void cache_slice(const LayerArgs& a, const CheckRows<
     e -= nd;
     off = (long)(cr.pb + e / qp) * qd + e % qp;
   }
-  lds_copy16(static_cast<const unsigned char*>(a.C) + off * 16, cr.cache, e0);
+  lds_copy16(static_cast<const unsigned char*>(a.C) + off * 16, reinterpret_cast<unsigned char*>(cr.cache) + e0 * 16);
 }
 
 // Partial sums of the check rows. The rows are cut into units of kUnit columns and every wave takes

@@ -167,7 +167,7 @@ constexpr bool layer_takes_more(int nc, int rows) {
 // of its 13 rows over its lanes however few columns a lane has, so fewer, fuller waves run fewer
 // instructions; but every column is one more polled word per lane. In units of instructions of the
 // busiest SIMD: waves per SIMD times (13 per column plus the reduction's, about 64 in FP32 and 140 in
-// FP64), plus 90 per polled word: within 2 % of the best of the measured lane counts at each size (us per
+// FP64), plus 90 per polled word: within 2.5 % of the best of the measured lane counts at each size (us per
 // iteration at the rule's / 1024 / 640 / 512 / 256 lanes: 3200 FP32 rows 1.77 / 1.73 / 1.84 / - / -, 2400 rows
 // 1.65 / 1.68 / 1.63 / 1.65 / -, 800 rows 1.36 / 1.49 / 1.41 / 1.37 / 1.45; 800 FP64 rows 1.76 / 1.99 / 1.92 /
 // 1.76 / -, 156 rows 1.55 / 1.91 / 1.72 / 1.59 / 1.52; -: too few lanes for these columns).

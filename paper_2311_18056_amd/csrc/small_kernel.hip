@@ -53,11 +53,6 @@ struct Vec<double> {
   static constexpr int V = 2;
   typedef double2 type;
 };
-// 16 bytes per lane from memory to consecutive LDS bytes from lds (uniform).
-typedef __attribute__((address_space(3))) void* lds_ptr_t;
-__device__ __forceinline__ void lds_copy16(const void* src, void* lds) {
-  __builtin_amdgcn_global_load_lds(src, (lds_ptr_t)lds, 16, 0, 0);
-}
 template <typename T>
 __device__ __forceinline__ void load_vec(const T* p, T (&v)[Vec<T>::V]) {
   const typename Vec<T>::type t = *reinterpret_cast<const typename Vec<T>::type*>(p);
@@ -273,7 +268,7 @@ __global__ void __launch_bounds__(SB) small_kernel(LayerArgs a) {
       __syncthreads();
       double p = 0.0, unused, unused2, unused3;
       if (wave_rows) {
-        check_products<T, NI>(a, Cl, NT, s, n, cv, p, unused, unused2, unused3);  // rows past L hold zeros
+        check_products<T, NI>(a, Cl, NT, s, n, cv, p, unused, unused2, unused3);
         p = row_sum(p);
       }
       if (row && !xrow) {
