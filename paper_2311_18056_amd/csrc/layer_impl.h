@@ -196,11 +196,10 @@ __device__ __forceinline__ bool wait_f64(const uint64_t* p, uint32_t tag, double
 // Closed loop: the plant state after solve sv - 1, x_sv = Ad x_{sv-1} + Bd u_{sv-1}. Each
 // workgroup keeps its own copy of the state in xpl (parity sv & 1); u comes from the words the
 // first nu constraint-row owners published at the end of solve sv - 1 (tag utag), staged in
-// ucur. Each wave forms kPlantRows state entries per pass (their loads in flight together):
+// ucur. Each wave forms PR state entries per pass (their loads in flight together):
 // per entry, lane-strided FP64 products then a butterfly sum, the same order in every
 // workgroup, so every copy is the same. Returns false if the wait for u timed out.
-constexpr int kPlantRows = 4;
-template <int NWV>
+template <int NWV, int PR>
 __device__ __forceinline__ bool plant_step(const LayerArgs& a, int sv, uint32_t utag, double* ucur, int* flag) {
   const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
   const uint64_t* uw = a.xu + (long)((sv - 1) & 1) * a.nu * 2;
@@ -214,26 +213,26 @@ __device__ __forceinline__ bool plant_step(const LayerArgs& a, int sv, uint32_t 
   const double* xc = a.xpl + ((long)((sv - 1) & 1) * gridDim.x + blockIdx.x) * kMaxPlant;
   double* xn = a.xpl + ((long)(sv & 1) * gridDim.x + blockIdx.x) * kMaxPlant;
   const int nx = a.nx, nu = a.nu;
-  for (int rb = wave * kPlantRows; rb < nx; rb += NWV * kPlantRows) {
-    double dv[kPlantRows];
-    int rc[kPlantRows];  // a valid row index for every slot (entries past nx are not stored)
+  for (int rb = wave * PR; rb < nx; rb += NWV * PR) {
+    double dv[PR];
+    int rc[PR];  // a valid row index for every slot (entries past nx are not stored)
 #pragma unroll
-    for (int b = 0; b < kPlantRows; ++b) {
+    for (int b = 0; b < PR; ++b) {
       dv[b] = 0.0;
       rc[b] = rb + b < nx ? rb + b : nx - 1;
     }
     for (int c = lane; c < nx; c += kWave) {
       const double xv = xc[c];
 #pragma unroll
-      for (int b = 0; b < kPlantRows; ++b) dv[b] = fma(a.Ad[(long)rc[b] * nx + c], xv, dv[b]);
+      for (int b = 0; b < PR; ++b) dv[b] = fma(a.Ad[(long)rc[b] * nx + c], xv, dv[b]);
     }
     for (int c = lane; c < nu; c += kWave) {
       const double uv = ucur[c];
 #pragma unroll
-      for (int b = 0; b < kPlantRows; ++b) dv[b] = fma(a.Bd[(long)rc[b] * nu + c], uv, dv[b]);
+      for (int b = 0; b < PR; ++b) dv[b] = fma(a.Bd[(long)rc[b] * nu + c], uv, dv[b]);
     }
 #pragma unroll
-    for (int b = 0; b < kPlantRows; ++b) {
+    for (int b = 0; b < PR; ++b) {
 #pragma unroll
       for (int off = kWave / 2; off > 0; off >>= 1) dv[b] += __shfl_xor(dv[b], off, kWave);
       if (lane == 0 && rb + b < nx) xn[rb + b] = dv[b];
@@ -746,6 +745,12 @@ __global__ void __launch_bounds__(BS) layer_kernel(LayerArgs a_in) {
   const bool wave_last = wave_on && wave * kWave + cs * (NC - 1) < L;  // some lane's of the wave does
   const int my_row = rows_held<RP>(), my_row_e = rows_held<EB>();
   const bool writer = row_writer<RP>();
+  // Rows that the plant step and a loop's update of q, l, u take together, between solves, while the
+  // weights stay in registers: one where those hold more than 26 of them, else rows of weights go to scratch
+  // memory and back in every step (a step of two iterations of 400 / 800 FP64 rows took 9.9 / 10.7 us
+  // with 4 and 2 and takes 8.4 / 9.3, of 3200 / 4000 FP32 rows 18.7 / 27.4 and 17.1 / 23.7).
+  constexpr bool FULL = NRS * NC * words<T>() > 26;
+  constexpr int PR = FULL ? 1 : 4, UB = XT && FULL ? 1 : 2;
   if (tid == 0) fail_flag = 0;
   for (int i = tid; i < 2 * kMaxRows * NWAVE; i += BS) (&red[0][0][0])[i] = (T)0;  // waves without columns
   if (tid < a.n_rho) rt.grid[tid] = a.grid[tid];
@@ -836,7 +841,7 @@ __global__ void __launch_bounds__(BS) layer_kernel(LayerArgs a_in) {
       if (sv == 0) {
         for (int c = tid; c < a.nx; c += BS) xpl[c] = a.x0[c];
         __syncthreads();
-      } else if (!plant_step<NWAVE>(a, sv, tag - span, ucur, &fail_flag)) {
+      } else if (!plant_step<NWAVE, PR>(a, sv, tag - span, ucur, &fail_flag)) {
         if (tid == 0) err_raise(a.err, tag);
         finish<T, XT>(a, rs, r0, nrows, sv, 0, ST_INTERNAL, j, tag, exs);
         return;
@@ -848,7 +853,6 @@ __global__ void __launch_bounds__(BS) layer_kernel(LayerArgs a_in) {
       const double* x0 = closed ? xpl : a.x0 + (long)sv * a.nx;
       // rows 0 .. nrows-1: owned layer rows; rows nrows .. nrows+nck-1: the check's x rows
       // (UB rows of a wave at a time, their loads and lane sums interleaved)
-      constexpr int UB = 2;
       for (int rb = wave * UB; rb < nrows + nck; rb += NWAVE * UB) {
         double du[UB];
         const double* ar[UB];
@@ -1124,7 +1128,7 @@ __global__ void __launch_bounds__(BS) layer_kernel(LayerArgs a_in) {
   if (closed && g == 0) {
     const uint32_t last = a.tag + (uint32_t)(a.count - 1) * span;
     __syncthreads();
-    if (!plant_step<NWAVE>(a, a.count, last, ucur, &fail_flag)) {
+    if (!plant_step<NWAVE, PR>(a, a.count, last, ucur, &fail_flag)) {
       if (tid == 0) err_raise(a.err, last);
       return;
     }
@@ -1136,7 +1140,7 @@ __global__ void __launch_bounds__(BS) layer_kernel(LayerArgs a_in) {
 // The kernel for nc columns per lane, with layer_reg_rows or (more) layer_more_rows rows in registers.
 template <typename T, int NC, bool XT>
 const void* fn_at(bool more) {
-  constexpr int A = layer_reg_rows<T>(NC), B = layer_more_rows<T>(NC);
+  constexpr int A = layer_reg_rows<T>(NC), B = layer_more_rows<T>(NC, XT);
   return more ? reinterpret_cast<const void*>(&layer_kernel<T, NC, B, XT>)
               : reinterpret_cast<const void*>(&layer_kernel<T, NC, A, XT>);
 }

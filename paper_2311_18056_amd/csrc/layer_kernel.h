@@ -152,14 +152,16 @@ constexpr int layer_pass_rows(int nc) {
 // taken where it saves a pass: 200 iterations of 1600 FP32 rows at 20 / 24 / 32 rows a block took 524 / 687 /
 // 842 us with 13 rows in registers and take 453 / 452 / 454 with 32; at 3200 rows and 24 a block 876 and 673
 // with 16, but at 20 a block, one pass either way, 615 and 672: its rows cost registers and products too.
+// FP64 closed loops and scaled solves (xt) stop at 16, what else they hold leaves no room: 50 steps of 16
+// iterations of 144 rows at 16 a block took 1849 us with 32 and take 1607, at 32 a block 1796 and 2469.
 template <typename T>
-constexpr int layer_more_rows(int nc) {
-  const int most = (sizeof(T) == sizeof(double) ? 32 : 64) / nc / 16 * 16;
-  return most > 32 ? 32 : (most > layer_reg_rows<T>(nc) ? most : layer_reg_rows<T>(nc));
+constexpr int layer_more_rows(int nc, bool xt) {
+  const int most = 64 * 4 / (int)sizeof(T) / nc / 16 * 16, cap = xt && sizeof(T) == sizeof(double) ? 16 : 32;
+  return most > cap ? cap : (most > layer_reg_rows<T>(nc) ? most : layer_reg_rows<T>(nc));
 }
 template <typename T>
-constexpr bool layer_takes_more(int nc, int rows) {
-  const int pass = layer_pass_rows<T>(nc), a = rows - layer_reg_rows<T>(nc), b = rows - layer_more_rows<T>(nc);
+constexpr bool layer_takes_more(int nc, int rows, bool xt) {
+  const int pass = layer_pass_rows<T>(nc), a = rows - layer_reg_rows<T>(nc), b = rows - layer_more_rows<T>(nc, xt);
   return (b > 0 ? (b + pass - 1) / pass : 0) < (a > 0 ? (a + pass - 1) / pass : 0);
 }
 

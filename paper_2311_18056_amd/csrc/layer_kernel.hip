@@ -19,8 +19,8 @@ LaunchPlan plan_layer(int n, int m, int grid, bool xt) {
   if (L < 1 || L > kMaxLayerRows || grid < 1) return p;
   const int cs = layer_col_lanes<T>(L), nc = (L + cs - 1) / cs;
   const int rows = (L + grid - 1) / grid;
-  const bool more = layer_takes_more<T>(nc, rows);
-  const int reg = more ? layer_more_rows<T>(nc) : layer_reg_rows<T>(nc);
+  const bool more = layer_takes_more<T>(nc, rows, xt);
+  const int reg = more ? layer_more_rows<T>(nc, xt) : layer_reg_rows<T>(nc);
   const void* fn = sizeof(T) == sizeof(double) ? (xt ? layer_fn_f64x(nc, more) : layer_fn_f64(nc, more))
                                                : (xt ? layer_fn_f32x(nc, more) : layer_fn_f32(nc, more));
   int dev = 0, smem_max = 0, cus = 0;
