@@ -539,10 +539,10 @@ constexpr double kPlainRowsPerGroup = 12.5;
 
 // Rows per workgroup that closed loops and Ruiz-scaled solves aim at. Loops spend their steps on exchanges
 // and on short row updates that every further workgroup shares: us per step of two iterations at 6 / 8 / 10 /
-// 12.5 rows per workgroup and at one workgroup per compute unit, 800 FP64 rows 10.7 / 10.4 / 10.5 / 10.9 /
-// 11.2, 400 9.8 / 9.6 / 9.8 / 10.0 / 10.5, 1600 13.0 / 12.6 / 13.2 / 12.9 / 13.2; FP32 9.2 / 9.0 / 9.1 / 9.5 /
-// 9.9 at 800, 11.4 / 11.0 / 11.4 / 11.3 / 11.4 at 1600. Scaled solves depend on it less: us per iteration with
-// its checks, 800 FP64 rows 2.28 / 2.19 / 2.22 / 2.26 / 2.28, 800 FP32 rows 1.80 / 1.81 / 1.80 / 1.83 / 1.82.
+// 12.5 rows per workgroup and at one workgroup per compute unit, 400 FP64 rows 8.2 / 7.9 / 8.3 / 8.4 / 8.9, 800
+// 9.2 / 8.9 / 9.0 / 9.7 / 9.5, 1600 11.4 / 11.0 / 11.5 / 11.4 / 11.4; FP32 9.3 / 8.9 / 9.0 / 9.5 / 10.0 at 800,
+// 11.4 / 11.0 / 11.3 / 11.3 / 11.5 at 1600. Scaled solves depend on it less: us per iteration with its checks,
+// 800 FP64 rows 2.24 / 2.13 / 2.18 / 2.22 / 2.23, 800 FP32 rows 1.80 / 1.81 / 1.79 / 1.83 / 1.83.
 constexpr int kLoopRowsPerGroup = 8;
 
 int choose_grid(relu_qp_handle* h) {
