@@ -270,7 +270,9 @@ int relu_qp_set_tile(relu_qp_handle* h, int tile_rows);
  * relu_qp_footprint: the same figure for a handle that relu_qp_setup(n, m, s) would create,
  * plus F, E, lo, hi if nx > 0 (relu_qp_set_parametric), computed on the host without any
  * device call; *setup_extra (may be NULL) receives the FP64 workspace setup holds on top of
- * that while it factors. RQP_EINVAL for bad sizes or settings (as relu_qp_setup). */
+ * that while it factors: the penalties that are factored together take up to 1 GiB (at least one
+ * of them), and setup makes do with one at a time where the device has no room for that.
+ * RQP_EINVAL for bad sizes or settings (as relu_qp_setup). */
 int relu_qp_device_bytes(const relu_qp_handle* h, size_t* bytes);
 
 /* Spill and restore, so that a server can take a family out of HBM without losing its setup:
